@@ -119,11 +119,11 @@ Plan make_plan(const NetDesc& n, int n_e, int T, bool bf16) {
         }
         p.fc_wg = plan_split(p.B, fc_wgrad_tiles_bf16(n.arch), 64, wg_target);
     } else {
-        p.sel_fc = plan_split(n.flat, fc_fwd_tiles(n.arch, n_e), 32, fc_fwd_target_wgs(n_e));
-        p.trn_fc = plan_split(n.flat, fc_fwd_tiles(n.arch, p.Bp), 32, fc_fwd_target_wgs(p.Bp));
+        p.sel_fc = fc_fwd_plan(n.arch, n_e);
+        p.trn_fc = fc_fwd_plan(n.arch, p.Bp);
         for (int l = 1; l < n.n_conv; ++l)
             p.wg[l] = plan_split(p.B * n.conv[l].ho * n.conv[l].wo, conv_wgrad_tiles(n.arch, l), 64, 256);
-        p.fc_wg = plan_split(p.B, fc_wgrad_tiles(n.arch), 32, 256);
+        p.fc_wg.n = 1; p.fc_wg.k_per = 0;
     }
     // the first layer's weight gradient runs in the direct kernel, one partial per workgroup: three
     // (bf16) or one and a half (fp32, larger LDS tile) workgroups per compute unit, at most one per band
@@ -459,7 +459,7 @@ hipError_t enqueue_train(paac_ctx* c, hipStream_t s, bool prof, const TrainArgs&
     } else {
         L.run(K_TRN_FC_BWD, [&] {
             return fc_bwd(L.s, n.arch, (const float*)b.act[last], (const float*)b.dh, b.theta + a.fc_w, (float*)b.dact[last],
-                          fc_pw, b.fc_pb, p.B, p.fc_wg);
+                          fc_pw, b.fc_pb, p.B);
         });
     }
     // conv backward, last layer first
@@ -475,12 +475,10 @@ hipError_t enqueue_train(paac_ctx* c, hipStream_t s, bool prof, const TrainArgs&
         }
         if (l == 0)
             L.run(wg_id, [&] { return conv1_wgrad_direct(L.s, n.arch, !bf16, x.states, b.dact[0], b.pw[0], b.pb[0], p.B, p.wg[0].n); });
-        else if (bf16) L.run(wg_id, [&] { return conv_wgrad_bf16(L.s, n.arch, l, in, (const bf16_t*)b.dact[l], b.pw[l], b.pb[l], p.B, p.wg[l]); });
-        else L.run(wg_id, [&] { return conv_wgrad(L.s, n.arch, l, in, (const float*)b.dact[l], b.pw[l], b.pb[l], p.B, p.wg[l]); });
+        else L.run(wg_id, [&] { return conv_wgrad_bf16(L.s, n.arch, l, in, (const bf16_t*)b.dact[l], b.pw[l], b.pb[l], p.B, p.wg[l]); });
         if (l > 0) {
             const int dg_id = l == 2 ? K_TRN_CONV3_DG : K_TRN_CONV2_DG;
-            if (bf16) L.run(dg_id, [&] { return conv_dgrad_bf16(L.s, n.arch, l, (const bf16_t*)b.dact[l], b.wd[l], (const bf16_t*)b.act[l - 1], (bf16_t*)b.dact[l - 1], p.B); });
-            else L.run(dg_id, [&] { return conv_dgrad(L.s, n.arch, l, (const float*)b.dact[l], b.theta + a.conv_w[l], (const float*)b.act[l - 1], (float*)b.dact[l - 1], p.B); });
+            L.run(dg_id, [&] { return conv_dgrad_bf16(L.s, n.arch, l, (const bf16_t*)b.dact[l], b.wd[l], (const bf16_t*)b.act[l - 1], (bf16_t*)b.dact[l - 1], p.B); });
         }
     }
     // reduce split gradients, global norm, clip + RMSProp

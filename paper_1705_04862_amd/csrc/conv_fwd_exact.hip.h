@@ -255,15 +255,6 @@ __global__ __launch_bounds__(256, 1) void conv_fwd_exact_kernel(const float* __r
     }
 }
 
-inline int device_cus() {
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-    }
-    return cus;
-}
-
 template <class G>
 inline hipError_t launch_conv_fwd_exact(hipStream_t s, const float* in, const bf16_t* Wp, const float* bias, float* out, int ns) {
     if (ns <= 0) return hipErrorInvalidValue;

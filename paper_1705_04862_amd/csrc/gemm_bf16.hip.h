@@ -150,6 +150,16 @@ __device__ __forceinline__ uint4 u8x8_to_bf16(uint2 w) {
                       u8pair_to_bf16(cv(w.y, 0), cv(w.y, 8)), u8pair_to_bf16(cv(w.y, 16), cv(w.y, 24)));
 }
 
+// compute units of the device (256 where there is none: plans are also made without one)
+inline int device_cus() {
+    static int cus = 0;
+    if (cus == 0) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
+    }
+    return cus;
+}
+
 template <int BM_, int BN_, int BK_, int WM_, int WN_, int STAGES_ = 3, int MINW_ = 2>
 struct TileB {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_, STAGES = STAGES_;

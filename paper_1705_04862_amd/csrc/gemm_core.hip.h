@@ -1,7 +1,6 @@
 // Tiled fp32 GEMM core on CDNA4 matrix cores (v_mfma_f32_32x32x2f32)
-// with functor-defined operand addressing, used for every dense contraction of the PAAC step:
-// convolution forward (implicit im2col rows), data gradient (gather form), weight gradient
-// (reduction over output positions, split over workgroups) and the fully connected layer.
+// with functor-defined operand addressing, used for the forward contractions of batches too small for the
+// exact-operand kernels: convolution (implicit im2col rows) and the fully connected layer.
 //
 //   C[m][n] = sum_k A(m,k) * B(k,n)          m < M, n < N, k in this workgroup's k-range
 //
@@ -84,13 +83,6 @@ struct Tile {
 
 template <class E, class = void> struct AuxEarly { static constexpr bool value = false; };
 template <class E> struct AuxEarly<E, std::enable_if_t<E::kAuxEarly>> { static constexpr bool value = true; };
-// Epilogues whose element address is a sum of a row part and a column part declare kSplitAddr and give
-//   int row_part(int row, int z) const; int col_part(int col, int z) const;   (element offsets)
-//   const float* mask() const; float* dst() const;      out[rp + cp] = mask[rp + cp] > 0 ? v : 0
-// A thread then computes 16 row parts and one column part per fragment instead of the address of every
-// element twice (its divisions by the geometry's constants were most of a scatter epilogue's instructions).
-template <class E, class = void> struct SplitAddr { static constexpr bool value = false; };
-template <class E> struct SplitAddr<E, std::enable_if_t<E::kSplitAddr>> { static constexpr bool value = true; };
 template <class L, class = void> struct RowFast { static constexpr bool value = false; };
 template <class L> struct RowFast<L, std::enable_if_t<L::kRowFast>> { static constexpr bool value = true; };
 template <class L> __host__ __device__ constexpr bool row_fast() { return RowFast<L>::value; }
@@ -236,8 +228,6 @@ __device__ __forceinline__ void gemm_body(const AL& al, const BL& bl, const EP& 
 #pragma unroll
                 for (int r = 0; r < MM::NACC; ++r) acc[q][i][j][r] = 0.f;
 
-    float colsum = 0.f;   // used only when EP::kColSum (bias gradient = column sums of B)
-
     const int fidx = lane % MF, fk = lane / MF;
     const int a_base = wm * (TM * MF) + fidx, b_base = wn * (TN * MF) + fidx;
 
@@ -302,12 +292,6 @@ __device__ __forceinline__ void gemm_body(const AL& al, const BL& bl, const EP& 
                 }
             }(), ...);
         }(std::make_integer_sequence<int, NS>());
-        if constexpr (EP::kColSum) {
-            if (mt == 0 && tid < BN) {
-#pragma unroll 8
-                for (int k = 0; k < BK; ++k) colsum += BL::kContig ? bs[tid * LDB + k] : bs[k * LDB + tid];
-            }
-        }
     };
 
     // one pipeline step for the tile in register-stage position G (= kt % S)
@@ -321,6 +305,7 @@ __device__ __forceinline__ void gemm_body(const AL& al, const BL& bl, const EP& 
     // Auxiliary epilogue operands (bias, ReLU mask) do not depend on the accumulators: their loads are
     // issued before the first operand load, so the epilogue does not start with a memory round trip
     // (about a microsecond, a tenth of a small-batch kernel).
+    static_assert(!EP::kColSum, "no column sums here");
     typename EP::Aux aux[TM][TN][MM::NACC];
     auto load_aux = [&]() {
 #pragma unroll
@@ -336,39 +321,6 @@ __device__ __forceinline__ void gemm_body(const AL& al, const BL& bl, const EP& 
             }
     };
     if constexpr (AuxEarly<EP>::value) load_aux();      // one register per column (a bias); masks would cost 16
-    // Scatter epilogues with a mask (data gradients): the addresses and the mask values of the wave's fragments
-    // are fetched before the first operand load where a wave owns one fragment (16 registers each), so that the
-    // epilogue, which is on the critical path of the fused backward launches, does not start with a memory round
-    // trip; with more fragments per wave they are fetched after the k loop.
-    int sat[SplitAddr<EP>::value ? TM : 1][TN][MM::NACC];
-    float smk[SplitAddr<EP>::value ? TM : 1][TN][MM::NACC];
-    constexpr bool MASK_EARLY = TM * TN == 1;         // two fragments per wave (64 registers): measured slower, 31.7 -> 38.1 us
-    auto load_masks = [&]() __attribute__((always_inline)) {
-      if constexpr (SplitAddr<EP>::value) {
-        int cp[TN]; bool cok[TN];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int col = n0 + wn * (TN * MF) + j * MF + MM::col(lane);
-            cok[j] = col < N;
-            cp[j] = ep.col_part(cok[j] ? col : 0, z);
-        }
-        const float* const mk = ep.mask();
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < MM::NACC; ++r) {
-                const int row = m0 + wm * (TM * MF) + i * MF + MM::row(r, lane);
-                const bool rok = wk == 0 && row < M;
-                const int rp = ep.row_part(rok ? row : 0, z);
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    sat[i][j][r] = rok && cok[j] ? rp + cp[j] : -1;
-                    smk[i][j][r] = mk[sat[i][j][r] >= 0 ? sat[i][j][r] : 0];
-                }
-            }
-      }
-    };
-    if constexpr (SplitAddr<EP>::value && MASK_EARLY) load_masks();
     gload(0, std::integral_constant<int, 0>());
     gload(1, std::integral_constant<int, 1>());
     if constexpr (S > 2) gload(2, std::integral_constant<int, 2>());
@@ -394,9 +346,6 @@ __device__ __forceinline__ void gemm_body(const AL& al, const BL& bl, const EP& 
         }
     }
 
-    if constexpr (EP::kColSum) {
-        if (mt == 0 && tid < BN && n0 + tid < N) ep.store_colsum(n0 + tid, colsum, z);
-    }
     if constexpr (KACC == 2) {
 #pragma unroll
         for (int r = 0; r < MM::NACC; ++r) acc[0][0][0][r] += acc[1][0][0][r];
@@ -428,18 +377,6 @@ __device__ __forceinline__ void gemm_body(const AL& al, const BL& bl, const EP& 
 #pragma unroll
                     for (int r = 0; r < MM::NACC; ++r) acc[0][i][j][r] += src[((i * TN + j) * MM::NACC + r) * 64];
         }
-    }
-    if constexpr (SplitAddr<EP>::value) {
-        if constexpr (!MASK_EARLY) load_masks();
-        float* const out = ep.dst();
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < MM::NACC; ++r)
-                    if (sat[i][j][r] >= 0) out[sat[i][j][r]] = smk[i][j][r] > 0.f ? acc[0][i][j][r] : 0.f;
-        return;
     }
     if constexpr (!AuxEarly<EP>::value) load_aux();     // every auxiliary load of the tile, then the stores
 #pragma unroll
@@ -533,102 +470,6 @@ struct DenseKCols {
     }
 };
 
-// Data gradient, gather form.  Row = (n, yy, xx) of parity class z = (py, px); k = (ty, tx, co);
-// value = dY[n][yy - ty][xx - tx][co] when that output position exists, else 0.
-template <class G> struct DgradGatherRowsK {
-    static constexpr bool kContig = true;
-    typedef float4 Raw;
-    static __device__ __forceinline__ float4 finish(Raw r, bool ok) { return keep_if(ok, r); }
-    const float* dy; int rows;
-    struct Fixed { const float* p; int yy, xx; bool ok; };
-    __device__ __forceinline__ Fixed prep(int row, int) const {
-        Fixed f; f.ok = row < rows;
-        row = f.ok ? row : 0;
-        const int n = row / (G::HC * G::WC), r = row % (G::HC * G::WC);
-        f.yy = r / G::WC; f.xx = r % G::WC;
-        f.p = dy + (size_t)n * (G::HO * G::WO * G::COUT);
-        return f;
-    }
-    __device__ __forceinline__ Raw load(const Fixed& f, int k, bool pred, bool& ok) const {
-        ok = pred && f.ok;
-        k = ok ? k : 0;
-        const int tap = k / G::COUT, co = k % G::COUT, ty = tap / G::TAPS, tx = tap % G::TAPS;
-        int oy = f.yy - ty, ox = f.xx - tx;
-        ok = ok && oy >= 0 && oy < G::HO && ox >= 0 && ox < G::WO;
-        oy = ok ? oy : 0; ox = ok ? ox : 0;
-        return *reinterpret_cast<const float4*>(f.p + (oy * G::WO + ox) * G::COUT + co);
-    }
-};
-
-// Weights seen by the data gradient: B(k = (ty,tx,co), n = ci) = W[(ky,kx,ci)][co] with
-// ky = py + ST*ty, kx = px + ST*tx for parity class z = py*ST + px.
-template <class G> struct DgradWeightColsK {
-    static constexpr bool kContig = true;
-    typedef float4 Raw;
-    static __device__ __forceinline__ float4 finish(Raw r, bool ok) { return keep_if(ok, r); }
-    const float* w;
-    struct Fixed { const float* p; int py, px; bool ok; };
-    __device__ __forceinline__ Fixed prep(int ci, int z) const {
-        Fixed f; f.py = z / G::ST; f.px = z % G::ST; f.ok = ci < G::CIN;
-        f.p = w + (size_t)(f.ok ? ci : 0) * G::COUT;
-        return f;
-    }
-    __device__ __forceinline__ Raw load(const Fixed& f, int k, bool pred, bool& ok) const {
-        ok = pred && f.ok;
-        k = ok ? k : 0;
-        const int tap = k / G::COUT, co = k % G::COUT, ty = tap / G::TAPS, tx = tap % G::TAPS;
-        const int ky = f.py + G::ST * ty, kx = f.px + G::ST * tx;
-        return *reinterpret_cast<const float4*>(f.p + (size_t)(ky * G::KS + kx) * (G::CIN * G::COUT) + co);
-    }
-};
-
-// The same with all ST*ST parity classes as columns, n = (z, ci): the classes of one block of input
-// positions read the same gathered dY rows, so one GEMM with N = ST*ST*CIN gathers them once.
-template <class G> struct DgradWeightColsKAll {
-    static constexpr bool kContig = true;
-    typedef float4 Raw;
-    static __device__ __forceinline__ float4 finish(Raw r, bool ok) { return keep_if(ok, r); }
-    const float* w;
-    struct Fixed { const float* p; int py, px; bool ok; };
-    __device__ __forceinline__ Fixed prep(int col, int) const {
-        Fixed f; f.ok = col < G::ST * G::ST * G::CIN;
-        col = f.ok ? col : 0;
-        const int z = col / G::CIN, ci = col % G::CIN;
-        f.py = z / G::ST; f.px = z % G::ST;
-        f.p = w + (size_t)ci * G::COUT;
-        return f;
-    }
-    __device__ __forceinline__ Raw load(const Fixed& f, int k, bool pred, bool& ok) const {
-        ok = pred && f.ok;
-        k = ok ? k : 0;
-        const int tap = k / G::COUT, co = k % G::COUT, ty = tap / G::TAPS, tx = tap % G::TAPS;
-        const int ky = f.py + G::ST * ty, kx = f.px + G::ST * tx;
-        return *reinterpret_cast<const float4*>(f.p + (size_t)(ky * G::KS + kx) * (G::CIN * G::COUT) + co);
-    }
-};
-
-// Weight gradient of the later conv layers: A(m = (ky,kx,c), k = output position) from NHWC input.
-template <class G> struct ConvNHWCKCols {
-    static constexpr bool kContig = false;
-    typedef float4 Raw;
-    static __device__ __forceinline__ float4 finish(Raw r, bool ok) { return keep_if(ok, r); }
-    const float* x; int rows;
-    struct Fixed { int off; bool ok; };
-    __device__ __forceinline__ Fixed prep(int col, int) const {
-        Fixed f; f.ok = col < G::KK;
-        col = f.ok ? col : 0;
-        const int ky = col / (G::KS * G::CIN), rem = col % (G::KS * G::CIN);
-        f.off = ky * (G::W * G::CIN) + rem;
-        return f;
-    }
-    __device__ __forceinline__ Raw load(const Fixed& f, int row, bool pred, bool& ok) const {
-        ok = pred && f.ok && row < rows;
-        row = ok ? row : 0;
-        const int n = row / (G::HO * G::WO), r = row % (G::HO * G::WO), oy = r / G::WO, ox = r % G::WO;
-        return *reinterpret_cast<const float4*>(x + ((size_t)(n * G::H + oy * G::ST) * G::W + ox * G::ST) * G::CIN + f.off);
-    }
-};
-
 // ----------------------------------------------------------------------------------------------
 // Epilogues
 struct EpiBiasRelu {            // out[row][col] = max(v + bias[col], 0)
@@ -654,67 +495,6 @@ template <bool COLSUM> struct EpiPartial {   // out[z][row][col] = v ; optional 
     }
 };
 
-template <class G> struct EpiDgradMask {     // scatter a parity class back to NHWC, times ReLU'
-    static constexpr bool kColSum = false, kSplitAddr = true;
-    typedef float Aux;
-    float* dx; const float* act;
-    __device__ __forceinline__ int row_part(int row, int) const {
-        const int n = row / (G::HC * G::WC), r = row % (G::HC * G::WC), yy = r / G::WC, xx = r % G::WC;
-        return ((n * G::H + yy * G::ST) * G::W + xx * G::ST) * G::CIN;
-    }
-    __device__ __forceinline__ int col_part(int col, int z) const { return ((z / G::ST) * G::W + z % G::ST) * G::CIN + col; }
-    __device__ __forceinline__ const float* mask() const { return act; }
-    __device__ __forceinline__ float* dst() const { return dx; }
-    __device__ __forceinline__ size_t addr(int row, int col, int z) const {
-        const int py = z / G::ST, px = z % G::ST;
-        const int n = row / (G::HC * G::WC), r = row % (G::HC * G::WC), yy = r / G::WC, xx = r % G::WC;
-        return ((size_t)(n * G::H + yy * G::ST + py) * G::W + xx * G::ST + px) * G::CIN + col;
-    }
-    __device__ __forceinline__ Aux aux(int row, int col, int z, bool ok) const { return act[ok ? addr(row, col, z) : 0]; }
-    __device__ __forceinline__ void store(int row, int col, float v, int z, Aux a) const {
-        dx[addr(row, col, z)] = a > 0.f ? v : 0.f;
-    }
-};
-
-template <class G> struct EpiDgradMaskAll {  // the same for columns n = (z, ci) of all parity classes
-    static constexpr bool kColSum = false, kSplitAddr = true;
-    typedef float Aux;
-    float* dx; const float* act;
-    __device__ __forceinline__ int row_part(int row, int) const {
-        const int n = row / (G::HC * G::WC), r = row % (G::HC * G::WC), yy = r / G::WC, xx = r % G::WC;
-        return ((n * G::H + yy * G::ST) * G::W + xx * G::ST) * G::CIN;
-    }
-    __device__ __forceinline__ int col_part(int col, int) const {
-        const int z = col / G::CIN, ci = col % G::CIN;
-        return ((z / G::ST) * G::W + z % G::ST) * G::CIN + ci;
-    }
-    __device__ __forceinline__ const float* mask() const { return act; }
-    __device__ __forceinline__ float* dst() const { return dx; }
-    __device__ __forceinline__ size_t addr(int row, int col) const {
-        const int z = col / G::CIN, ci = col % G::CIN, py = z / G::ST, px = z % G::ST;
-        const int n = row / (G::HC * G::WC), r = row % (G::HC * G::WC), yy = r / G::WC, xx = r % G::WC;
-        return ((size_t)(n * G::H + yy * G::ST + py) * G::W + xx * G::ST + px) * G::CIN + ci;
-    }
-    __device__ __forceinline__ Aux aux(int row, int col, int, bool ok) const { return act[ok ? addr(row, col) : 0]; }
-    __device__ __forceinline__ void store(int row, int col, float v, int, Aux a) const {
-        dx[addr(row, col)] = a > 0.f ? v : 0.f;
-    }
-};
-
-struct EpiDenseMask {           // out[row][col] = act[row][col] > 0 ? v : 0
-    static constexpr bool kColSum = false, kSplitAddr = true;
-    typedef float Aux;
-    float* out; const float* act; int ld;
-    __device__ __forceinline__ int row_part(int row, int) const { return row * ld; }
-    __device__ __forceinline__ int col_part(int col, int) const { return col; }
-    __device__ __forceinline__ const float* mask() const { return act; }
-    __device__ __forceinline__ float* dst() const { return out; }
-    __device__ __forceinline__ Aux aux(int row, int col, int, bool ok) const { return act[ok ? (size_t)row * ld + col : 0]; }
-    __device__ __forceinline__ void store(int row, int col, float v, int, Aux a) const {
-        out[(size_t)row * ld + col] = a > 0.f ? v : 0.f;
-    }
-};
-
 // ----------------------------------------------------------------------------------------------
 // Workgroup ids are dealt round-robin to the eight XCDs, each with an L2 of its own.  xcd_order
 // renumbers them so that the workgroups of one XCD take consecutive positions in the tile order:
@@ -732,50 +512,6 @@ __global__ __launch_bounds__(T::NT) void gemm_kernel(const AL al, const BL bl, c
     int id = blockIdx.x + gridDim.x * blockIdx.y;         // dispatch order: x fastest
     id = xcd_order(id, gridDim.x * gridDim.y);
     gemm_body<T, AL, BL, EP>(al, bl, ep, M, N, K, k_per_split, m_tiles, id % (int)gridDim.x, id / (int)gridDim.x, smem);
-}
-
-// A GEMM with its launch shape, as a value: lets two independent GEMMs share one launch.
-template <class T_, class AL_, class BL_, class EP_> struct GemmCall {
-    typedef T_ T; typedef AL_ AL; typedef BL_ BL; typedef EP_ EP;
-    AL al; BL bl; EP ep;
-    int M, N, K, z_count, k_per_split;
-    __host__ __device__ int m_tiles() const { return (M + T::BM - 1) / T::BM; }
-    __host__ __device__ int tiles() const { return m_tiles() * ((N + T::BN - 1) / T::BN); }
-    __host__ __device__ int blocks() const { return tiles() * z_count; }
-};
-template <class T, class AL, class BL, class EP>
-inline GemmCall<T, AL, BL, EP> make_call(const AL& al, const BL& bl, const EP& ep, int M, int N, int K, int z, int k_per) {
-    return GemmCall<T, AL, BL, EP>{al, bl, ep, M, N, K, z, k_per};
-}
-
-// Two independent GEMMs in one grid: workgroups [0, a.blocks()) run `a`, the rest run `b`.  At small
-// batch each GEMM alone leaves most compute units idle and is bound by its own start-up and drain
-// latencies; side by side they overlap them.
-template <class C1, class C2>
-__global__ __launch_bounds__(256) void gemm_pair_kernel(const C1 a, const C2 b) {
-    static_assert(C1::T::NT == 256 && C2::T::NT == 256, "both halves run on four wavefronts");
-    constexpr int S1 = gemm_smem_floats<typename C1::T, typename C1::AL, typename C1::BL>();
-    constexpr int S2 = gemm_smem_floats<typename C2::T, typename C2::AL, typename C2::BL>();
-    __shared__ __attribute__((aligned(16))) float smem[S1 > S2 ? S1 : S2];
-    const int n1 = a.blocks();
-    if ((int)blockIdx.x < n1) {
-        const int t = a.tiles();
-        const int id = xcd_order(blockIdx.x, n1);
-        gemm_body<typename C1::T, typename C1::AL, typename C1::BL, typename C1::EP>(
-            a.al, a.bl, a.ep, a.M, a.N, a.K, a.k_per_split, a.m_tiles(), id % t, id / t, smem);
-    } else {
-        const int t = b.tiles();
-        const int r = xcd_order(blockIdx.x - n1, (int)gridDim.x - n1);
-        gemm_body<typename C2::T, typename C2::AL, typename C2::BL, typename C2::EP>(
-            b.al, b.bl, b.ep, b.M, b.N, b.K, b.k_per_split, b.m_tiles(), r % t, r / t, smem);
-    }
-}
-
-template <class C1, class C2>
-inline hipError_t launch_pair(hipStream_t s, const C1& a, const C2& b) {
-    if (a.blocks() <= 0 || b.blocks() <= 0) return hipErrorInvalidValue;
-    launch_k((gemm_pair_kernel<C1, C2>), dim3(a.blocks() + b.blocks(), 1, 1), dim3(256), s, a, b);
-    return hipGetLastError();
 }
 
 template <class T, class AL, class BL, class EP>

@@ -25,7 +25,7 @@ __global__ __launch_bounds__(KW * 64) void gemm_reg16_kernel(const AL al, const 
                                                              int K, int k_per_split, int m_tiles, int n_fast) {
     typedef Mma<16> MM;
     static_assert(AL::kContig, "operand A is read along k");
-    static_assert(!EP::kColSum && !SplitAddr<EP>::value, "plain epilogues only");
+    static_assert(!EP::kColSum, "plain epilogues only");
     __shared__ __attribute__((aligned(16))) float red[(KW - 1) * TN * 64 * 4];
 
     int id = blockIdx.x + gridDim.x * blockIdx.y;

@@ -42,28 +42,17 @@ Split plan_split(int k_total, int tiles, int granule, int target_wgs);
 // later layers read float NHWC (k = ky,kx,c).
 hipError_t conv_fwd(hipStream_t s, int arch, int layer, const void* in, const float* W, const float* b,
                     float* out, int ns);
-// dX = dY (*) W^T in gather form, multiplied by ReLU'(act_in); layer >= 1.
-hipError_t conv_dgrad(hipStream_t s, int arch, int layer, const float* dy, const float* W,
-                      const float* act_in, float* dx, int ns);
-// partial_w[split][K][c_out], partial_b[split][c_out]; rows of the reduction are output positions.
-int conv_wgrad_tiles(int arch, int layer);
-hipError_t conv_wgrad(hipStream_t s, int arch, int layer, const void* in, const float* dy, float* partial_w,
-                      float* partial_b, int ns, Split sp);
 // fc forward: partial[split][ns][fc] = x[ns][flat(k-range)] . W[flat][fc]   (no bias, no ReLU)
-int fc_fwd_tiles(int arch, int ns);
-int fc_fwd_target_wgs(int ns);
+Split fc_fwd_plan(int arch, int ns);
 hipError_t fc_fwd(hipStream_t s, int arch, const float* x, const float* W, float* partial, int ns, Split sp);
-// dx[ns][flat] = (dh[ns][fc] . W^T) * 1[act > 0]
-hipError_t fc_dgrad(hipStream_t s, int arch, const float* dh, const float* W, const float* act, float* dx, int ns);
-// partial_w[split][flat][fc] = x^T . dh over a range of samples; partial_b[split][fc] = column sums of dh
-int fc_wgrad_tiles(int arch);
-hipError_t fc_wgrad(hipStream_t s, int arch, const float* x, const float* dh, float* partial_w, float* partial_b,
-                    int ns, Split sp);
-// fused data + weight gradient of one layer (one launch)
+hipError_t fc_fwd_ws(hipStream_t s, int arch, const float* x, const float* W, float* partial, int ns, Split sp);     // its part from 65 rows on
+// fused data + weight gradient of one layer in one launch (layers_ws.hip):
+// dx = dY (*) W^T times ReLU'(act_in); partial_w[split][K][c_out], partial_b[split][c_out]
+int conv_wgrad_tiles(int arch, int layer);
 hipError_t conv_bwd(hipStream_t s, int arch, int layer, const float* act_in, const float* dy, const float* W, float* dx,
                     float* pw, float* pb, int ns, Split sp);
-hipError_t fc_bwd(hipStream_t s, int arch, const float* x, const float* dh, const float* W, float* dx, float* pw, float* pb,
-                  int ns, Split sp);
+// dx[ns][flat] = (dh[ns][fc] . W^T) * 1[x > 0]; pw[flat][fc] = x^T . dh, pb[fc] = column sums of dh
+hipError_t fc_bwd(hipStream_t s, int arch, const float* x, const float* dh, const float* W, float* dx, float* pw, float* pb, int ns);
 
 // ---- the same layers with bf16 operands (layers_bf16.hip): bf16 NHWC activations, bf16 weight copies
 // (forward copy Wt[c_out][K], data-gradient copy Wd[c_in][ky,kx][c_out]; fc: Wt[fc][flat], Wc[flat][fc]),

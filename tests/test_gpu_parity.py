@@ -224,6 +224,31 @@ def test_train_nature_above_one_sample_per_compute_unit(paac, oracle):
     check_train(oracle, net, ctx, params, rms, ro, I.HParams(lr=0.002), "nature_52x5")
 
 
+@pytest.mark.parametrize("net,n_e,t_max", [
+    # every tile of the wave-specialised backward GEMMs, ragged last tiles, the row counts at which a layer changes its
+    # tile (nature: 30 | 31, 61 | 62, 75 | 76, 122 | 123, 150 | 151, 192 | 193; nips: 61 | 62, 122 | 123) and one row
+    (I.nature_net(6), 1, 1), (I.nature_net(6), 15, 2), (I.nature_net(6), 31, 1), (I.nature_net(6), 61, 1), (I.nature_net(6), 31, 2),
+    (I.nature_net(6), 25, 3), (I.nature_net(6), 38, 2), (I.nature_net(6), 61, 2), (I.nature_net(6), 41, 3), (I.nature_net(6), 151, 1),
+    (I.nature_net(6), 193, 1), (I.nature_net(6), 77, 5), (I.nips_net(6), 61, 1), (I.nips_net(6), 31, 2), (I.nips_net(6), 123, 1), (I.nips_net(6), 257, 1)],
+    ids=lambda v: v.name if isinstance(v, I.Net) else str(v))
+def test_train_fp32_backward_tiles(paac, oracle, net, n_e, t_max):
+    """Gradients against the oracle with the ReLU decisions that the forward pass took (a unit within rounding of
+    zero may take the other side in double precision, which is no matter of the backward pass)."""
+    ctx = make_ctx(paac, net, n_e, t_max)
+    params = I.make_params(31, net, bias_range=0.05)
+    rms = I.make_rms(31, net, hi=0.01)
+    ro = I.make_rollout(31, net, n_e, t_max, 0.05)
+    hp = I.HParams(lr=0.002)
+    ctx.set_state(params, rms)
+    ctx.train_step(dev(ro.states), dev(ro.actions), dev(ro.rewards), dev(ro.dones), hp)
+    torch.cuda.synchronize()
+    g = ctx.get_state()[2]
+    want = oracle.train_step(net, params, rms, ro.states, ro.actions, ro.rewards, ro.dones, hp, masks=hip_relu_masks(ctx, net))
+    for name, sl in net.param_slices().items():
+        ref = want.grads[sl]
+        assert np.linalg.norm(g[sl].astype(np.float64) - ref) <= 2e-5 * max(np.linalg.norm(ref), 0.05 * np.linalg.norm(want.grads)), name
+
+
 def test_train_first_step_from_zero_state_and_paper_hparams(paac, oracle):
     """Fresh optimiser state, zero biases, the paper's clipping threshold of 40."""
     cfg = I.CONFIGS[0]
