@@ -166,22 +166,9 @@ def main():
         torch.cuda.synchronize()
         return time.perf_counter() - t0
 
-    # Launch mode: the library can replay captured HIP graphs (one per call) or launch its kernels one
-    # by one.  Which is faster depends on the host (a graph launch has a fixed cost per call, direct
-    # launches need a host that keeps ahead of the GPU): a short calibration picks the mode, the timed
-    # region then runs entirely in that mode.
     for i in range(args.warmup):
         step(i)
     k2 = max(10, args.steps // 10)
-    ms_graph = 1e3 * timed(k2) / k2
-    ctx.set_graphs(False)
-    for i in range(5):
-        step(i)
-    ms_eager = 1e3 * timed(k2) / k2
-    use_graphs = ms_graph <= ms_eager
-    ctx.set_graphs(use_graphs)
-    for i in range(5):
-        step(i)
     elapsed = timed(args.steps)
     ms_per_step = 1e3 * elapsed / args.steps
     value = args.steps * n_e * T / elapsed
@@ -271,12 +258,11 @@ def main():
         "dtype": "bf16" if cfg.precision == 1 else "f32", "data": "synthetic",
         "config": {"workload": cfg.name, "net": net.name, "n_e": n_e, "t_max": T, "n_actions": net.n_actions,
                    "rollouts_rotated": len(R), "algorithm": args.algorithm, "phase": args.phase,
-                   "launch": "hip-graph replay (t_max select graphs + 1 train graph)" if use_graphs else "direct kernel launches on one stream"},
+                   "launch": "direct kernel launches on one stream"},
         "roofline": roof,
         "step_gflop": round(step_flop / 1e9, 3),
         "pct_mfma_peak_whole_step": round(100 * step_flop / elapsed * args.steps / (mfma_peak * 1e12), 3),
         "ms_select_x_tmax": round(ms_select, 4), "ms_train": round(ms_train, 4),
-        "ms_per_step_graph_replay": round(ms_graph, 4), "ms_per_step_direct_launch": round(ms_eager, 4),
         "ms_per_step_with_activation_cache": round(ms_cached, 4),
         "kernels": per_kernel,
         "paper_context": "derived from the paper's Table 1 training times and time split on a GTX 980 Ti: "

@@ -1,5 +1,5 @@
 // C ABI of libpaac: context, workspace carving, parameter layout, the kernel sequences of
-// paac_select_actions / paac_train_step, HIP-graph capture and replay, per-kernel timing.
+// paac_select_actions / paac_train_step, per-kernel timing.
 #include "../../include/paac.h"
 #include "internal.h"
 
@@ -41,7 +41,6 @@ hipError_t scratch_for_device(int device, void** out) {
     return hipSuccess;
 }
 constexpr int kHpSlots = 16;
-constexpr int kMaxGraphs = 64;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 int pad64(int n) { return (n + 63) / 64 * 64; }
@@ -257,16 +256,6 @@ const char* const kKernelNames[K_COUNT] = {
     "train.clip_rmsprop", "train.bf16_weight_copies", "train.fc_bwd", "train.conv3_bwd", "train.conv2_bwd",
     "select.convs_fwd", "train.convs_fwd"};
 
-struct GraphKey {
-    int kind;                 // 0 select, 1 train
-    const void* p[6];
-    int algorithm; float epsilon;
-    bool operator==(const GraphKey& o) const {
-        return kind == o.kind && algorithm == o.algorithm && epsilon == o.epsilon && memcmp(p, o.p, sizeof(p)) == 0;
-    }
-};
-struct GraphEntry { GraphKey key; hipGraph_t graph; hipGraphExec_t exec; };
-
 }  // namespace
 
 struct paac_ctx {
@@ -276,7 +265,6 @@ struct paac_ctx {
     Plan plan;
     Buffers buf;
     hipStream_t stream;       // caller's stream: all work is enqueued here
-    hipStream_t cap_stream;   // private stream used only for graph capture
     int device;
     void* noalloc_scratch;    // this device's copy of the static scratch array
     bool have_params;
@@ -285,8 +273,7 @@ struct paac_ctx {
     int sel_count;            // select calls since the last train step / parameter load
     int algorithm;            // PAAC_ALG_*
     float epsilon;            // exploration rate of PAAC_ALG_NSTEP_Q
-    bool use_graphs, profiling;
-    std::vector<GraphEntry> graphs;
+    bool profiling;
     // hyper-parameter staging: pinned ring, one event per slot
     float* hp_pinned;
     hipEvent_t hp_ev[kHpSlots];
@@ -509,40 +496,16 @@ hipError_t enqueue_train(paac_ctx* c, hipStream_t s, bool prof, const TrainArgs&
     return L.err;
 }
 
+// Every call launches its kernels one by one.  A captured graph of the same kernels costs about 5 us more per
+// call on the GPU's side and hides nothing: the host enqueues a select call in 12 to 17 us, less than the
+// call runs (arch_nips, n_e = 32, t_max = 5, six calls per iteration: 186 us replayed, 153 us launched one by one).
 template <class Enq>
-int run_or_replay(paac_ctx* c, const GraphKey& key, Enq&& enq) {
+int launch_all(paac_ctx* c, Enq&& enq) {
     int err_id = -1;
-    if (c->profiling || !c->use_graphs) {
-        if (c->profiling && c->pending.size() > 16384) { int r = drain_profile(c); if (r) return r; }
-        hipError_t e = enq(c->stream, c->profiling, &err_id);
-        if (e != hipSuccess)
-            return fail(c, PAAC_E_HIP, std::string("launch of ") + (err_id >= 0 ? kKernelNames[err_id] : "?") + ": " + hipGetErrorString(e));
-        return PAAC_OK;
-    }
-    for (auto& g : c->graphs)
-        if (g.key == key) { HIP_TRY(c, hipGraphLaunch(g.exec, c->stream)); return PAAC_OK; }
-    if ((int)c->graphs.size() >= kMaxGraphs) {      // too many distinct argument tuples: launch directly
-        hipError_t e = enq(c->stream, false, &err_id);
-        if (e != hipSuccess) return fail(c, PAAC_E_HIP, std::string("launch: ") + hipGetErrorString(e));
-        return PAAC_OK;
-    }
-    // Capture on the private stream.  It must see everything already enqueued on the caller's stream
-    // only at replay time, and the replay is launched on the caller's stream, so no dependency is
-    // needed here.
-    GraphEntry ge{};
-    ge.key = key;
-    HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-    hipError_t e = enq(c->cap_stream, false, &err_id);
-    hipError_t e2 = hipStreamEndCapture(c->cap_stream, &ge.graph);
-    if (e != hipSuccess || e2 != hipSuccess) {
-        if (e2 == hipSuccess && ge.graph) hipGraphDestroy(ge.graph);
-        return fail(c, PAAC_E_HIP, std::string("graph capture failed at ") + (err_id >= 0 ? kKernelNames[err_id] : "end") +
-                                       ": " + hipGetErrorString(e != hipSuccess ? e : e2));
-    }
-    hipError_t e3 = hipGraphInstantiate(&ge.exec, ge.graph, nullptr, nullptr, 0);
-    if (e3 != hipSuccess) { hipGraphDestroy(ge.graph); return fail(c, PAAC_E_HIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e3)); }
-    c->graphs.push_back(ge);
-    HIP_TRY(c, hipGraphLaunch(ge.exec, c->stream));
+    if (c->profiling && c->pending.size() > 16384) { int r = drain_profile(c); if (r) return r; }
+    const hipError_t e = enq(c->stream, c->profiling, &err_id);
+    if (e != hipSuccess)
+        return fail(c, PAAC_E_HIP, std::string("launch of ") + (err_id >= 0 ? kKernelNames[err_id] : "?") + ": " + hipGetErrorString(e));
     return PAAC_OK;
 }
 
@@ -602,14 +565,13 @@ int paac_create(const paac_config* cfg, void* workspace_dev, size_t workspace_by
     c->buf = carve(c->net, c->arena, c->plan, cfg->precision == PAAC_PREC_BF16, static_cast<char*>(workspace_dev));
     if (c->buf.bytes > workspace_bytes) { delete c; return PAAC_E_WORKSPACE; }
     c->stream = static_cast<hipStream_t>(hip_stream);
-    c->have_params = false; c->have_train = false; c->use_graphs = true; c->profiling = false;
+    c->have_params = false; c->have_train = false; c->profiling = false;
     c->algorithm = PAAC_ALG_ACTOR_CRITIC; c->epsilon = 0.f;
     c->hp_next = 0; c->hp_valid = false;
     memset(c->hp_ev_used, 0, sizeof(c->hp_ev_used));
     memset(c->k_ms, 0, sizeof(c->k_ms)); memset(c->k_calls, 0, sizeof(c->k_calls));
     hipError_t e = hipGetDevice(&c->device);
     if (e == hipSuccess) e = scratch_for_device(c->device, &c->noalloc_scratch);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->hp_pinned), kHpSlots * HP_COUNT * sizeof(float), hipHostMallocDefault);
     for (int i = 0; i < kHpSlots && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&c->hp_ev[i], hipEventDisableTiming);
     if (e != hipSuccess) { delete c; return PAAC_E_HIP; }
@@ -620,12 +582,10 @@ int paac_create(const paac_config* cfg, void* workspace_dev, size_t workspace_by
 void paac_destroy(paac_ctx* c) {
     if (!c) return;
     hipStreamSynchronize(c->stream);
-    for (auto& g : c->graphs) { hipGraphExecDestroy(g.exec); hipGraphDestroy(g.graph); }
     for (auto& p : c->pending) { hipEventDestroy(p.a); hipEventDestroy(p.b); }
     for (auto e : c->ev_pool) hipEventDestroy(e);
     for (int i = 0; i < kHpSlots; ++i) hipEventDestroy(c->hp_ev[i]);
     if (c->hp_pinned) hipHostFree(c->hp_pinned);
-    if (c->cap_stream) hipStreamDestroy(c->cap_stream);
     delete c;
 }
 
@@ -708,11 +668,7 @@ int paac_select_actions(paac_ctx* c, const uint8_t* states_dev, const float* uni
     // cached rollout: calls 0 .. t_max-1 since the last train step fill slabs 0 .. t_max-1; further calls
     // use the bootstrap slab (the train step recomputes it) and make the cache invalid by their count
     const int slab = c->cache_on ? (c->sel_count < c->plan.T ? c->sel_count : c->plan.T) : -1;
-    GraphKey key{};
-    key.kind = 0; key.p[0] = states_dev; key.p[1] = uniforms_dev; key.p[2] = actions_dev; key.p[3] = values_dev; key.p[4] = probs_dev;
-    key.p[5] = reinterpret_cast<const void*>(static_cast<uintptr_t>(slab + 1));
-    key.algorithm = c->algorithm; key.epsilon = c->epsilon;
-    const int r = run_or_replay(c, key, [&](hipStream_t s, bool prof, int* id) { return enqueue_select(c, c->buf, s, prof, x, slab, id); });
+    const int r = launch_all(c, [&](hipStream_t s, bool prof, int* id) { return enqueue_select(c, c->buf, s, prof, x, slab, id); });
     if (r == PAAC_OK && c->cache_on && c->sel_count <= c->plan.T) ++c->sel_count;
     return r;
 }
@@ -763,11 +719,7 @@ int paac_train_step(paac_ctx* c, const uint8_t* states_dev, const int32_t* actio
     const bool cached = c->cache_on && c->sel_count == c->plan.T;
     c->sel_count = 0;
     c->have_train = true;
-    GraphKey key{};
-    key.kind = 1; key.p[0] = states_dev; key.p[1] = actions_dev; key.p[2] = rewards_dev; key.p[3] = dones_dev; key.p[4] = stats_dev;
-    key.p[5] = reinterpret_cast<const void*>(static_cast<uintptr_t>(cached ? 1 : 0));
-    key.algorithm = c->algorithm; key.epsilon = 0.f;
-    return run_or_replay(c, key, [&](hipStream_t s, bool prof, int* id) { return enqueue_train(c, s, prof, x, cached, id); });
+    return launch_all(c, [&](hipStream_t s, bool prof, int* id) { return enqueue_train(c, s, prof, x, cached, id); });
 }
 
 int paac_get_train_outputs(paac_ctx* c, float* logits_host, float* values_host, float* returns_host) {
@@ -845,11 +797,8 @@ int paac_set_algorithm(paac_ctx* c, int algorithm, float epsilon) {
     return PAAC_OK;
 }
 
-int paac_set_graphs(paac_ctx* c, int use_graphs) {
-    if (!c) return PAAC_E_NULL;
-    c->use_graphs = use_graphs != 0;
-    return PAAC_OK;
-}
+// accepted and without effect: see launch_all
+int paac_set_graphs(paac_ctx* c, int) { return c ? PAAC_OK : PAAC_E_NULL; }
 
 int paac_set_profiling(paac_ctx* c, int enabled) {
     if (!c) return PAAC_E_NULL;
