@@ -61,6 +61,8 @@ def kernel_work(net, n_e, t_max, act_bytes=4):
         w[f"train.conv{l + 1}_wgrad"] = ("flop", f * B)
         if l > 0:
             w[f"train.conv{l + 1}_dgrad"] = ("flop", f * B)
+    w["select.conv12_fwd"] = ("flop", sum(conv[:2]) * n_e)
+    w["train.conv12_fwd"] = ("flop", sum(conv[:2]) * Bp)
     w["select.convs_fwd"] = ("flop", sum(conv) * n_e)    # all convolutions of a sample in one workgroup
     w["train.convs_fwd"] = ("flop", sum(conv) * Bp)
     w["select.fc_fwd"] = ("flop", fc * n_e)

@@ -246,7 +246,7 @@ enum KernelId {
     K_TRN_CONV1, K_TRN_CONV2, K_TRN_CONV3, K_TRN_FC, K_TRN_HEADS, K_TRN_LOSS, K_TRN_HEADS_BWD,
     K_TRN_FC_WG, K_TRN_FC_DG, K_TRN_CONV3_WG, K_TRN_CONV3_DG, K_TRN_CONV2_WG, K_TRN_CONV2_DG, K_TRN_CONV1_WG,
     K_TRN_GRAD_REDUCE, K_TRN_RMSPROP, K_TRN_BF16W, K_TRN_FC_BWD, K_TRN_CONV3_BWD, K_TRN_CONV2_BWD,
-    K_SEL_TRUNK, K_TRN_TRUNK, K_COUNT
+    K_SEL_TRUNK, K_TRN_TRUNK, K_SEL_CONV12, K_TRN_CONV12, K_COUNT
 };
 const char* const kKernelNames[K_COUNT] = {
     "select.conv1_fwd", "select.conv2_fwd", "select.conv3_fwd", "select.fc_fwd", "select.heads_sample",
@@ -254,7 +254,7 @@ const char* const kKernelNames[K_COUNT] = {
     "train.heads_bwd", "train.fc_wgrad", "train.fc_dgrad", "train.conv3_wgrad",
     "train.conv3_dgrad", "train.conv2_wgrad", "train.conv2_dgrad", "train.conv1_wgrad", "train.grad_reduce_norm",
     "train.clip_rmsprop", "train.bf16_weight_copies", "train.fc_bwd", "train.conv3_bwd", "train.conv2_bwd",
-    "select.convs_fwd", "train.convs_fwd"};
+    "select.convs_fwd", "train.convs_fwd", "select.conv12_fwd", "train.conv12_fwd"};
 
 }  // namespace
 
@@ -355,7 +355,8 @@ constexpr int kExactMinSamples = 96;
 
 // Forward trunk shared by select and train: convs, fc partial sums.
 // `row0`: first row of the activation buffers this launch writes (0, or the slab of a cached rollout).
-void enqueue_trunk(paac_ctx* c, const Buffers& b, Launcher& L, const uint8_t* states, int ns, Split fc_split, int id0, int row0) {
+// `keep`: the activations are read later (by the backward pass).
+void enqueue_trunk(paac_ctx* c, const Buffers& b, Launcher& L, const uint8_t* states, int ns, Split fc_split, int id0, int row0, bool keep) {
     const NetDesc& n = c->net; const Arena& a = c->arena;
     const void* in = states;
     const bool bf16 = c->cfg.precision == PAAC_PREC_BF16;
@@ -372,6 +373,14 @@ void enqueue_trunk(paac_ctx* c, const Buffers& b, Launcher& L, const uint8_t* st
     } else
     for (int l = 0; l < n.n_conv; ++l) {
         void* out = act_at(l);
+        if (!bf16 && l == 0 && ns <= kConv12MaxSamples) {
+            out = act_at(1);
+            L.run(id0 == K_SEL_CONV1 ? K_SEL_CONV12 : K_TRN_CONV12, [&] {
+                return conv12_fwd(L.s, n.arch, states, b.splits.dst[0], b.theta + a.conv_b[0], keep ? (float*)act_at(0) : nullptr,
+                                  b.theta + a.conv_w[1], b.theta + a.conv_b[1], (float*)out, ns);
+            });
+            ++l;
+        } else
         if (bf16) L.run(id0 + l, [&] { return conv_fwd_bf16(L.s, n.arch, l, in, b.wt[l], b.theta + a.conv_b[l], (bf16_t*)out, ns); });
         else if (l == 0)
             L.run(id0, [&] { return conv1_fwd_exact(L.s, n.arch, states, b.splits.dst[0], b.theta + a.conv_b[0], (float*)out, ns); });
@@ -391,7 +400,7 @@ hipError_t enqueue_select(paac_ctx* c, const Buffers& b, hipStream_t s, bool pro
     const NetDesc& n = c->net; const Arena& a = c->arena; const Plan& p = c->plan;
     if (prof) delay_us(s, 250);
     const int row0 = slab >= 0 ? slab * p.n_e : 0;
-    enqueue_trunk(c, b, L, x.states, p.n_e, p.sel_fc, K_SEL_CONV1, row0);
+    enqueue_trunk(c, b, L, x.states, p.n_e, p.sel_fc, K_SEL_CONV1, row0, slab >= 0);
     HeadsArgs h{};
     h.fc_partial = b.fc_partial; h.n_split = p.sel_fc.n; h.split_stride = (size_t)p.n_e * n.fc;
     h.fc_b = b.theta + a.fc_b; h.pi_w = b.theta + a.pi_w; h.pi_b = b.theta + a.pi_b;
@@ -417,7 +426,7 @@ hipError_t enqueue_train(paac_ctx* c, hipStream_t s, bool prof, const TrainArgs&
     const int f_row0 = cached ? p.B : 0, f_rows = cached ? p.n_e : p.Bp;      // rows the forward pass still has to compute
     const Split f_split = cached ? p.sel_fc : p.trn_fc;
     const size_t sample_bytes = (size_t)c->cfg.in_c * c->cfg.in_h * c->cfg.in_w;
-    enqueue_trunk(c, b, L, x.states + (size_t)f_row0 * sample_bytes, f_rows, f_split, K_TRN_CONV1, f_row0);
+    enqueue_trunk(c, b, L, x.states + (size_t)f_row0 * sample_bytes, f_rows, f_split, K_TRN_CONV1, f_row0, true);
     HeadsArgs h{};
     h.fc_partial = b.fc_partial; h.n_split = f_split.n; h.split_stride = (size_t)f_rows * F;
     h.fc_b = b.theta + a.fc_b; h.pi_w = b.theta + a.pi_w; h.pi_b = b.theta + a.pi_b;

@@ -102,6 +102,10 @@ struct WeightMirrors {
 hipError_t conv1_fwd_exact(hipStream_t s, int arch, const uint8_t* x, const bf16_t* w_parts, const float* b, float* out, int ns);
 // layers 1.. of the fp32 path, one sample per workgroup, from the parts of weights and activations
 hipError_t conv_fwd_exact(hipStream_t s, int arch, int layer, const float* in, const bf16_t* w_parts, const float* b, float* out, int ns);
+// first two convolutions of the fp32 path in one launch, ns <= kConv12MaxSamples; out1 may be null (then only out2 is written)
+constexpr int kConv12MaxSamples = 64;
+hipError_t conv12_fwd(hipStream_t s, int arch, const uint8_t* x, const bf16_t* w1_parts, const float* b1, float* out1,
+                      const float* W2, const float* b2, float* out2, int ns);
 // all convolutions of the fp32 path in one launch, one workgroup per sample; ns <= trunk_fwd_exact_max()
 int trunk_fwd_exact_max();
 hipError_t trunk_fwd_exact(hipStream_t s, int arch, const uint8_t* x, const bf16_t* const* w_parts, const float* const* b, float* const* out, int ns);

@@ -5,6 +5,7 @@
 #include "conv_dgrad_direct.hip.h"
 #include "conv_fwd_direct.hip.h"
 #include "conv_fwd_exact.hip.h"
+#include "conv12_fwd.hip.h"
 #include "conv_wgrad_direct.hip.h"
 #include "internal.h"
 
@@ -65,6 +66,13 @@ int trunk_fwd_exact_max() { return device_cus(); }
 hipError_t trunk_fwd_exact(hipStream_t s, int arch, const uint8_t* x, const bf16_t* const* w, const float* const* b, float* const* out, int ns) {
     if (arch == 0) return launch_trunk_fwd_exact<NipsC1, NipsC2, NoLayer>(s, x, w[0], b[0], out[0], w[1], b[1], out[1], nullptr, nullptr, nullptr, ns);
     return launch_trunk_fwd_exact<NatC1, NatC2, NatC3>(s, x, w[0], b[0], out[0], w[1], b[1], out[1], w[2], b[2], out[2], ns);
+}
+
+// First two convolutions of the fp32 path in one launch (see conv12_fwd_kernel).
+hipError_t conv12_fwd(hipStream_t s, int arch, const uint8_t* x, const bf16_t* w1_parts, const float* b1, float* out1,
+                      const float* W2, const float* b2, float* out2, int ns) {
+    if (arch == 0) return launch_conv12_fwd<NipsC1, NipsC2>(s, x, w1_parts, b1, out1, W2, b2, out2, ns);
+    return launch_conv12_fwd<NatC1, NatC2>(s, x, w1_parts, b1, out1, W2, b2, out2, ns);
 }
 
 // First convolution's weight gradient straight from the image (see conv1_wgrad_direct_kernel): dy is

@@ -171,6 +171,18 @@ def test_select_ragged_shapes(paac, oracle, net, n_e):
     check_select(oracle, net, params, st, u, run_select(ctx, net, st, u))
 
 
+@pytest.mark.parametrize("net,sizes", [(I.nips_net(6), (14, 15, 28, 29, 42, 43, 64)),
+                                       (I.nature_net(6), (7, 8, 14, 15, 21, 22, 42, 43, 64, 65))], ids=lambda p: getattr(p, "name", ""))
+def test_select_first_two_layers_band_splits(paac, oracle, net, sizes):
+    """Both sides of every change of the split of the first two convolutions."""
+    params = I.make_params(13, net, bias_range=0.05)
+    for n_e in sizes:
+        ctx = make_ctx(paac, net, n_e, 1)
+        ctx.set_state(params)
+        ro = I.make_rollout(100 + n_e, net, n_e, 1, 0.0)
+        check_select(oracle, net, params, ro.states[0], ro.uniforms[0], run_select(ctx, net, ro.states[0], ro.uniforms[0]))
+
+
 def test_select_extreme_pixels(paac, oracle):
     net = I.nips_net(6)
     ctx = make_ctx(paac, net, 3, 1)
