@@ -6,6 +6,7 @@
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
+#include <algorithm>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -192,13 +193,13 @@ Buffers carve(const NetDesc& n, const Arena& a, const Plan& p, bool bf16, char* 
     if (bf16) {
         WeightCopies& w = b.copies;
         auto copy = [&](bf16_t*& dst, int src_off, int K, int C, int cin, int mode) {
-            const int count = mode == 3 ? K * 32 : K * C;       // mode 3 pads the columns to 32
+            const int count = mode == 3 ? K * std::max(C, 32) : K * C;       // mode 3 pads the columns to 32
             dst = reinterpret_cast<bf16_t*>(take(((size_t)count + 1) / 2));
             w.dst[w.n] = dst; w.start[w.n] = w.total; w.src_off[w.n] = src_off; w.K[w.n] = K; w.C[w.n] = C;
             w.cin[w.n] = cin; w.mode[w.n] = mode; w.total += count; ++w.n;
         };
         for (int l = 0; l < n.n_conv; ++l) {
-            copy(b.wt[l], a.conv_w[l], n.conv[l].kk, n.conv[l].cout, n.conv[l].cin, l == 0 ? 3 : 0);
+            copy(b.wt[l], a.conv_w[l], n.conv[l].kk, n.conv[l].cout, n.conv[l].cin, 3);
             if (l > 0) copy(b.wd[l], a.conv_w[l], n.conv[l].kk, n.conv[l].cout, n.conv[l].cin, 2);
         }
         copy(b.fc_t, a.fc_w, n.flat, n.fc, 1, 0);
@@ -358,36 +359,48 @@ constexpr int kExactMinSamples = 96;
 // `keep`: the activations are read later (by the backward pass).
 void enqueue_trunk(paac_ctx* c, const Buffers& b, Launcher& L, const uint8_t* states, int ns, Split fc_split, int id0, int row0, bool keep) {
     const NetDesc& n = c->net; const Arena& a = c->arena;
-    const void* in = states;
+    const void* in;
     const bool bf16 = c->cfg.precision == PAAC_PREC_BF16;
     auto act_at = [&](int l) {
         const size_t per = (size_t)n.conv[l].ho * n.conv[l].wo * n.conv[l].cout * (bf16 ? 2 : 4);
         return static_cast<char*>(b.act[l]) + (size_t)row0 * per;
     };
-    if (!bf16 && ns >= kExactMinSamples && ns <= trunk_fwd_exact_max()) {
-        // one workgroup per sample runs all convolutions (exact bf16 parts)
-        const bf16_t* w[3] = {}; const float* bs[3] = {}; float* outs[3] = {};
-        for (int l = 0; l < n.n_conv; ++l) { w[l] = b.splits.dst[l]; bs[l] = b.theta + a.conv_b[l]; outs[l] = (float*)act_at(l); }
-        L.run(id0 == K_SEL_CONV1 ? K_SEL_TRUNK : K_TRN_TRUNK, [&] { return trunk_fwd_exact(L.s, n.arch, states, w, bs, outs, ns); });
-        in = outs[n.n_conv - 1];
-    } else
-    for (int l = 0; l < n.n_conv; ++l) {
-        void* out = act_at(l);
-        if (!bf16 && l == 0 && ns <= kConv12MaxSamples) {
-            out = act_at(1);
-            L.run(id0 == K_SEL_CONV1 ? K_SEL_CONV12 : K_TRN_CONV12, [&] {
+    const bool select = id0 == K_SEL_CONV1;
+    if (bf16 || (ns >= kExactMinSamples && ns <= trunk_fwd_exact_max())) {
+        // one workgroup runs all convolutions of a sample
+        const float* bs[3] = {}; const bf16_t* w[3] = {};
+        for (int l = 0; l < n.n_conv; ++l) { w[l] = bf16 ? b.wt[l] : b.splits.dst[l]; bs[l] = b.theta + a.conv_b[l]; }
+        L.run(select ? K_SEL_TRUNK : K_TRN_TRUNK, [&] {
+            if (bf16) {
+                bf16_t* outs[3] = {};
+                for (int l = 0; l < n.n_conv; ++l) outs[l] = keep || l == n.n_conv - 1 ? (bf16_t*)act_at(l) : nullptr;
+                return conv_trunk_bf16(L.s, n.arch, states, w, bs, outs, ns);
+            }
+            float* outs[3] = {};
+            for (int l = 0; l < n.n_conv; ++l) outs[l] = (float*)act_at(l);
+            return trunk_fwd_exact(L.s, n.arch, states, w, bs, outs, ns);
+        });
+        in = act_at(n.n_conv - 1);
+    } else {
+        int l = 0;
+        if (ns <= kConv12MaxSamples) {
+            L.run(select ? K_SEL_CONV12 : K_TRN_CONV12, [&] {
                 return conv12_fwd(L.s, n.arch, states, b.splits.dst[0], b.theta + a.conv_b[0], keep ? (float*)act_at(0) : nullptr,
-                                  b.theta + a.conv_w[1], b.theta + a.conv_b[1], (float*)out, ns);
+                                  b.theta + a.conv_w[1], b.theta + a.conv_b[1], (float*)act_at(1), ns);
             });
-            ++l;
-        } else
-        if (bf16) L.run(id0 + l, [&] { return conv_fwd_bf16(L.s, n.arch, l, in, b.wt[l], b.theta + a.conv_b[l], (bf16_t*)out, ns); });
-        else if (l == 0)
-            L.run(id0, [&] { return conv1_fwd_exact(L.s, n.arch, states, b.splits.dst[0], b.theta + a.conv_b[0], (float*)out, ns); });
-        else if (ns >= kExactMinSamples)
-            L.run(id0 + l, [&] { return conv_fwd_exact(L.s, n.arch, l, (const float*)in, b.splits.dst[l], b.theta + a.conv_b[l], (float*)out, ns); });
-        else L.run(id0 + l, [&] { return conv_fwd(L.s, n.arch, l, in, b.theta + a.conv_w[l], b.theta + a.conv_b[l], (float*)out, ns); });
-        in = out;
+            l = 2;
+        } else {
+            L.run(id0, [&] { return conv1_fwd_exact(L.s, n.arch, states, b.splits.dst[0], b.theta + a.conv_b[0], (float*)act_at(0), ns); });
+            l = 1;
+        }
+        for (; l < n.n_conv; ++l) {
+            L.run(id0 + l, [&] {
+                return ns >= kExactMinSamples
+                    ? conv_fwd_exact(L.s, n.arch, l, (const float*)act_at(l - 1), b.splits.dst[l], b.theta + a.conv_b[l], (float*)act_at(l), ns)
+                    : conv_fwd(L.s, n.arch, l, act_at(l - 1), b.theta + a.conv_w[l], b.theta + a.conv_b[l], (float*)act_at(l), ns);
+            });
+        }
+        in = act_at(n.n_conv - 1);
     }
     if (bf16) L.run(id0 + 3, [&] { return fc_fwd_bf16(L.s, n.arch, (const bf16_t*)in, b.fc_t, b.fc_partial, ns, fc_split); });
     else L.run(id0 + 3, [&] { return fc_fwd(L.s, n.arch, (const float*)in, b.theta + a.fc_w, b.fc_partial, ns, fc_split); });

@@ -9,8 +9,7 @@
 // the lanes read their B fragments (WeightSplits); the activations are split once, when a sample is
 // written into LDS as three images.
 //
-// Layout and wave roles are those of the bf16 kernel (conv_fwd_direct_kernel): position-major images
-// with the channels contiguous, de-interleaved by the parity of x for the stride-2 layer, pitch an odd
+// Position-major images with the channels contiguous, de-interleaved by the parity of x for the stride-2 layer, pitch an odd
 // multiple of 16 bytes; waves = (32-wide block of output channels) x (share of the k-steps), weights
 // in registers, k-shares added through LDS, bias + ReLU results leave through an fp32 LDS image as
 // contiguous 16-byte stores.

@@ -58,8 +58,6 @@ hipError_t fc_bwd(hipStream_t s, int arch, const float* x, const float* dh, cons
 // (forward copy Wt[c_out][K], data-gradient copy Wd[c_in][ky,kx][c_out]; fc: Wt[fc][flat], Wc[flat][fc]),
 // fp32 bias, fp32 partial sums and gradients ----
 typedef unsigned short bf16_t;
-hipError_t conv_fwd_bf16(hipStream_t s, int arch, int layer, const void* in, const bf16_t* Wt, const float* b,
-                         bf16_t* out, int ns);
 hipError_t conv_dgrad_bf16(hipStream_t s, int arch, int layer, const bf16_t* dy, const bf16_t* Wd, const bf16_t* act_in,
                            bf16_t* dx, int ns);
 int conv_wgrad_tiles_bf16(int arch, int layer);
@@ -102,6 +100,8 @@ struct WeightMirrors {
 hipError_t conv1_fwd_exact(hipStream_t s, int arch, const uint8_t* x, const bf16_t* w_parts, const float* b, float* out, int ns);
 // layers 1.. of the fp32 path, one sample per workgroup, from the parts of weights and activations
 hipError_t conv_fwd_exact(hipStream_t s, int arch, int layer, const float* in, const bf16_t* w_parts, const float* b, float* out, int ns);
+// all convolutions of the bf16 path in one launch; out[l] of a layer before the last may be null (then it is not written)
+hipError_t conv_trunk_bf16(hipStream_t s, int arch, const uint8_t* x, const bf16_t* const* w, const float* const* b, bf16_t* const* out, int ns);
 // first two convolutions of the fp32 path in one launch, ns <= kConv12MaxSamples; out1 may be null (then only out2 is written)
 constexpr int kConv12MaxSamples = 64;
 hipError_t conv12_fwd(hipStream_t s, int arch, const uint8_t* x, const bf16_t* w1_parts, const float* b1, float* out1,

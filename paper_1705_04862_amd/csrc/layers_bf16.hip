@@ -3,9 +3,9 @@
 #include "conv1_direct.hip.h"
 #include "conv1_wgrad_direct.hip.h"
 #include "conv_dgrad_direct.hip.h"
-#include "conv_fwd_direct.hip.h"
 #include "conv_fwd_exact.hip.h"
 #include "conv12_fwd.hip.h"
+#include "conv_trunk_bf16.hip.h"
 #include "conv_wgrad_direct.hip.h"
 #include "internal.h"
 
@@ -32,18 +32,10 @@ template <> struct TileBForN<16> { typedef B128x32 type; };
 template <> struct TileBForN<32> { typedef B128x32 type; };
 
 // ---------------------------------------------------------------------------------- forward
-// first layer: bytes straight from the image; layers 2 and 3: one sample at a time from LDS
-hipError_t conv_fwd_bf16(hipStream_t s, int arch, int layer, const void* in, const bf16_t* Wt, const float* b,
-                         bf16_t* out, int ns) {
-    if (arch == 0) {
-        if (layer == 0) return launch_conv1_direct<NipsC1>(s, (const uint8_t*)in, Wt, b, out, ns);
-        if (layer == 1) return launch_conv_fwd_direct<NipsC2>(s, (const bf16_t*)in, Wt, b, out, ns);
-    } else {
-        if (layer == 0) return launch_conv1_direct<NatC1>(s, (const uint8_t*)in, Wt, b, out, ns);
-        if (layer == 1) return launch_conv_fwd_direct<NatC2>(s, (const bf16_t*)in, Wt, b, out, ns);
-        if (layer == 2) return launch_conv_fwd_direct<NatC3>(s, (const bf16_t*)in, Wt, b, out, ns);
-    }
-    return hipErrorInvalidValue;
+// All convolutions in one launch (see conv_trunk_bf16_kernel); w[l], b[l], out[l] of layer l.
+hipError_t conv_trunk_bf16(hipStream_t s, int arch, const uint8_t* x, const bf16_t* const* w, const float* const* b, bf16_t* const* out, int ns) {
+    if (arch == 0) return launch_conv_trunk_bf16<NipsC1, NipsC2, NoThirdLayer>(s, x, w, b, out, ns);
+    return launch_conv_trunk_bf16<NatC1, NatC2, NatC3>(s, x, w, b, out, ns);
 }
 
 // First convolution of the fp32 path: bf16 matrix cores on exact operands (see conv1_exact_kernel).
@@ -195,7 +187,7 @@ hipError_t fc_wgrad_bf16(hipStream_t s, int arch, const bf16_t* x, const bf16_t*
 //   mode 0: dst[c*K + k]              = src[k*C + c]           (forward: [c_out][K])
 //   mode 1: dst[i]                    = src[i]                 (fc data gradient: [flat][fc])
 //   mode 2: dst[(ci*T + t)*C + co]    = src[(t*CIN + ci)*C + co]   (conv data gradient: [ci][ky,kx][co])
-//   mode 3: dst[(k/8)*256 + c*8 + k%8] = src[k*C + c], zero for c in [C, 32)   (first layer forward: the
+//   mode 3: dst[((k/8)*max(C, 32) + c)*8 + k%8] = src[k*C + c], zero for c in [C, 32)   (conv forward: the
 //           order in which the lanes read their MFMA B fragments, one contiguous KB per wave and load)
 __global__ __launch_bounds__(256) void make_bf16_weights_kernel(const WeightCopies w, const float* theta) {
     const int i = blockIdx.x * 256 + threadIdx.x;
@@ -209,7 +201,7 @@ __global__ __launch_bounds__(256) void make_bf16_weights_kernel(const WeightCopi
     if (w.mode[sidx] == 0) { const int c = o / K, k = o % K; si = k * C + c; }
     else if (w.mode[sidx] == 1) si = o;
     else if (w.mode[sidx] == 3) {
-        const int c = (o % 256) / 8, k = (o / 256) * 8 + o % 8;
+        const int row = 8 * max(C, 32), c = o % row / 8, k = o / row * 8 + o % 8;
         if (c >= C) { w.dst[sidx][o] = 0; return; }
         si = k * C + c;
     } else {

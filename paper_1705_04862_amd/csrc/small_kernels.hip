@@ -853,7 +853,7 @@ __global__ __launch_bounds__(256) void rmsprop_update_kernel(int n4, float4* the
                     if (mode == 0 || mode == 3) {          // k-contiguous: one 16-byte store
                         const uint4 w = make_uint4(bf(tv[0]) | (bf(tv[1]) << 16), bf(tv[2]) | (bf(tv[3]) << 16),
                                                    bf(tv[4]) | (bf(tv[5]) << 16), bf(tv[6]) | (bf(tv[7]) << 16));
-                        const size_t at = mode == 0 ? (size_t)c * K + k8 * 8 : (size_t)k8 * 256 + c * 8;
+                        const size_t at = mode == 0 ? (size_t)c * K + k8 * 8 : ((size_t)k8 * max(C, 32) + c) * 8;
                         *reinterpret_cast<uint4*>(dst + at) = w;
                     } else if (mode == 1) {                // the matrix as it is: lanes write consecutive columns
 #pragma unroll

@@ -563,6 +563,17 @@ def test_bf16_small_shapes(paac, oracle, net, n_e, t_max):
     check_train_bf16(oracle, net, ctx, params, rms, ro, I.HParams(), "bf16")
 
 
+@pytest.mark.parametrize("net,sizes", [(I.nips_net(6), (1, 256, 513)), (I.nature_net(6), (2, 256, 257, 513))], ids=lambda p: getattr(p, "name", ""))
+def test_bf16_forward_samples_per_workgroup(paac, oracle, net, sizes):
+    """None, one and two further samples for a workgroup of the convolution kernel, and workgroups without one."""
+    params = I.make_params(17, net, bias_range=0.05)
+    for n_e in sizes:
+        ctx = make_ctx(paac, net, n_e, 1, precision=1)
+        ctx.set_state(params)
+        ro = I.make_rollout(200 + n_e, net, n_e, 1, 0.0)
+        check_select_bf16(oracle, net, params, ro.states[0], ro.uniforms[0], run_select(ctx, net, ro.states[0], ro.uniforms[0]))
+
+
 def test_bf16_config3_full_size(paac, oracle):
     """Configuration 3 (n_e=256, t_max=5, Nature net) at full size against the whole oracle step."""
     cfg = I.CONFIGS[3]
