@@ -377,7 +377,7 @@ void enqueue_trunk(paac_ctx* c, const Buffers& b, Launcher& L, const uint8_t* st
                 return conv_trunk_bf16(L.s, n.arch, states, w, bs, outs, ns);
             }
             float* outs[3] = {};
-            for (int l = 0; l < n.n_conv; ++l) outs[l] = (float*)act_at(l);
+            for (int l = 0; l < n.n_conv; ++l) outs[l] = keep || l == n.n_conv - 1 ? (float*)act_at(l) : nullptr;
             return trunk_fwd_exact(L.s, n.arch, states, w, bs, outs, ns);
         });
         in = act_at(n.n_conv - 1);

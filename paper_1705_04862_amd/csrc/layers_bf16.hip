@@ -1,6 +1,6 @@
 // Dense layers of the PAAC network with bf16 operands (bf16 activations and weight copies, fp32
 // accumulation and fp32 gradients): the same six contractions as layers.hip on the bf16 GEMM core.
-#include "conv1_direct.hip.h"
+#include "conv1_exact.hip.h"
 #include "conv1_wgrad_direct.hip.h"
 #include "conv_dgrad_direct.hip.h"
 #include "conv_fwd_exact.hip.h"
