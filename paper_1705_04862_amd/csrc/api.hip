@@ -352,6 +352,8 @@ struct TrainArgs { const uint8_t* states; const int32_t* actions; const float* r
 
 // fp32 configuration, layers 1..: from this many samples on a launch takes the kernel that works one
 // sample per workgroup on exact bf16 parts; below, the tiled fp32 GEMM fills the chip better.
+// (Selections that keep nothing take it from 65 on, where the first two layers no longer share a launch: 80 samples of
+// arch_nature 39.2 -> 31 us, arch_nips 21.6 -> 20.)
 constexpr int kExactMinSamples = 96;
 
 // Forward trunk shared by select and train: convs, fc partial sums.
@@ -366,7 +368,8 @@ void enqueue_trunk(paac_ctx* c, const Buffers& b, Launcher& L, const uint8_t* st
         return static_cast<char*>(b.act[l]) + (size_t)row0 * per;
     };
     const bool select = id0 == K_SEL_CONV1;
-    if (bf16 || (ns >= kExactMinSamples && ns <= trunk_fwd_exact_max())) {
+    const int trunk_min = keep ? kExactMinSamples : kConv12MaxSamples + 1;
+    if (bf16 || (ns >= trunk_min && ns <= trunk_fwd_exact_max())) {
         // one workgroup runs all convolutions of a sample
         const float* bs[3] = {}; const bf16_t* w[3] = {};
         for (int l = 0; l < n.n_conv; ++l) { w[l] = bf16 ? b.wt[l] : b.splits.dst[l]; bs[l] = b.theta + a.conv_b[l]; }
