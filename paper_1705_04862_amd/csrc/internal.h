@@ -160,7 +160,8 @@ constexpr int kMaxSeg = 12;
 // Gradient reduction: one segment per parameter tensor.  A workgroup of the reduction belongs to one
 // segment; a thread owns four consecutive elements and, in segments with many splits, one of eight
 // split lanes (lanes[s] = 8: the splits q = j, j + 8, ... go to lane j, the eight lanes are added as
-// a tree), so that a tensor with hundreds of partial sums is not summed by a handful of threads.
+// a tree), so that a tensor with hundreds of partial sums is not summed by a handful of threads;
+// lanes[s] = 0: at most 32 elements without 16-byte alignment, one workgroup.
 struct GradSegments {
     int n;
     const float* partial[kMaxSeg]; int n_split[kMaxSeg]; size_t stride[kMaxSeg];
@@ -172,9 +173,9 @@ inline int plan_reduce_blocks(GradSegments& g) {
     int blocks = 0;
     for (int s = 0; s < g.n; ++s) {
         const bool vec = (reinterpret_cast<uintptr_t>(g.partial[s]) & 15) == 0 && (g.stride[s] & 3) == 0 && (g.count[s] & 3) == 0;
-        g.lanes[s] = (vec && g.n_split[s] >= 32) ? 8 : 1;
+        g.lanes[s] = (vec && g.n_split[s] >= 32) ? 8 : (!vec && g.n_split[s] > 8 && g.count[s] <= 32) ? 0 : 1;
         g.blk_off[s] = blocks;
-        blocks += (g.padded[s] / 4 * g.lanes[s] + 255) / 256;
+        blocks += g.lanes[s] == 0 ? 1 : (g.padded[s] / 4 * g.lanes[s] + 255) / 256;
     }
     g.blk_off[g.n] = blocks;
     return blocks;

@@ -691,7 +691,30 @@ __global__ __launch_bounds__(256) void grad_reduce_norm_kernel(const GradSegment
     float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
     bool owner = true;
     int local;
-    if (seg.lanes[sidx] == 1) {
+    if (seg.lanes[sidx] == 0) {
+        // a few elements that cannot be read 16 bytes at a time: a thread per element and accumulator (the thread that
+        // owns four elements would walk through all their splits one element after the other: 20 us at 128 splits,
+        // the whole of a launch that otherwise takes 10)
+        __shared__ float sums[32];
+        const int e = tid >> 3, j = tid & 7;
+        float a = 0.f;
+        if (e < count) {
+            const float* p = seg.partial[sidx] + e;
+            for (int q = j; q < ns; q += 8 * 16) {
+                float v[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[r] = p[(size_t)min(q + 8 * r, ns - 1) * st];        // clamped: ignored below
+#pragma unroll
+                for (int r = 0; r < 16; ++r) if (q + 8 * r < ns) a += v[r];
+            }
+        }
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1) a += __shfl_xor(a, o);    // the same tree as below
+        if (j == 0) sums[e] = a;
+        __syncthreads();
+        local = tid * 4;
+        if (local < 32) g = make_float4(sums[local], sums[local + 1], sums[local + 2], sums[local + 3]);
+    } else if (seg.lanes[sidx] == 1) {
         local = (lb * 256 + tid) * 4;
         if (local < padded) {
             const float* p = seg.partial[sidx] + local;
@@ -803,70 +826,81 @@ __global__ __launch_bounds__(256) void rmsprop_update_kernel(int n4, float4* the
                                                              StatsOut* stats_a, StatsOut* stats_b,
                                                              const WeightMirrors ws, int ws_blocks) {
     __shared__ float red[256];
-    float part = 0.f;
-    for (int q = threadIdx.x; q < n_ss; q += 256) part += block_ss[q];
-    const float tot = block_sum_256(part, red);
-    const float norm = sqrtf(tot);
+    float norm, scale;
     const float clip = hp[HP_CLIP], lr = hp[HP_LR], alpha = hp[HP_ALPHA], eps = hp[HP_EPS];
-    const float scale = norm > clip ? clip / norm : 1.0f;
     const float oma = 1.0f - alpha;
+    // The norm is a chain of its own (some 2000 partial sums, then a block sum) in front of every update: its loads go
+    // out all at once, behind the first parameters' (fp32, 1.7 M parameters, 2200 partial sums: 11.5 -> 9.5 us; one load after the other
+    // the chain was 4 us).
+    auto find_norm = [&]() __attribute__((always_inline)) {
+        constexpr int R = 12;
+        float part = 0.f;
+        for (int q = threadIdx.x; q < n_ss; q += 256 * R) {
+            float v[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r] = block_ss[min(q + 256 * r, n_ss - 1)];             // clamped: ignored below
+#pragma unroll
+            for (int r = 0; r < R; ++r) if (q + 256 * r < n_ss) part += v[r];
+        }
+        norm = sqrtf(block_sum_256(part, red));
+        scale = norm > clip ? clip / norm : 1.0f;
+    };
     // The matrices of ws are updated by the first ws_blocks workgroups, one thread per (eight
     // consecutive k, column): lanes along the columns read and write whole rows, and a thread holds
-    // exactly the eight values of one 16-byte slot of a part buffer or of a k-contiguous bf16 copy.
+    // exactly the eight values of one 16-byte slot of a part buffer or of a k-contiguous bf16 copy.  A workgroup's
+    // units are up to 64 columns wide and as many eights of k high as that leaves: the slots of a column in a
+    // k-contiguous copy are neighbours and leave the compute unit's L2 as one piece (bf16, 1.7 M parameters: 16 -> 14 us).
     if ((int)blockIdx.x < ws_blocks) {
-        int u = blockIdx.x * 256 + threadIdx.x;
-        for (int l = 0; l < ws.n; ++l) {
-            const int C = ws.C[l], K = ws.K[l], units = (K >> 3) * C;
-            if (u < units) {
-                const int k8 = u / C, c = u % C;
-                float* th = reinterpret_cast<float*>(theta); float* v2 = reinterpret_cast<float*>(g2);
-                const float* gr = reinterpret_cast<const float*>(grads);
-                float gv[8], vv[8], tv[8];
+        int blk = blockIdx.x, l = 0;
+        while (blk >= (ws.K[l] >> 3) * ws.C[l] / 256) { blk -= (ws.K[l] >> 3) * ws.C[l] / 256; ++l; }
+        const int C = ws.C[l], K = ws.K[l];
+        const int cw = min(C, 64), kh = 256 / cw, across = C / cw;            // a workgroup's columns and eights of k, workgroups across
+        const int k8 = blk / across * kh + threadIdx.x / cw, c = blk % across * cw + threadIdx.x % cw;
+        float* th = reinterpret_cast<float*>(theta); float* v2 = reinterpret_cast<float*>(g2);
+        const float* gr = reinterpret_cast<const float*>(grads);
+        float gv[8], vv[8], tv[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int at = ws.off[l] + (k8 * 8 + j) * C + c;
-                    gv[j] = gr[at]; vv[j] = v2[at]; tv[j] = th[at];
-                }
-                unsigned hi[4], mid[4], lo[4];
+        for (int j = 0; j < 8; ++j) {
+            const int at = ws.off[l] + (k8 * 8 + j) * C + c;
+            gv[j] = gr[at]; vv[j] = v2[at]; tv[j] = th[at];
+        }
+        find_norm();
+        unsigned hi[4], mid[4], lo[4];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int at = ws.off[l] + (k8 * 8 + j) * C + c;
-                    const float g = gv[j] * scale;
-                    vv[j] = alpha * vv[j] + oma * g * g;
-                    tv[j] -= lr * g / sqrtf(vv[j] + eps);
-                    v2[at] = vv[j]; th[at] = tv[j];
-                }
-                if (ws.split[l]) {
+        for (int j = 0; j < 8; ++j) {
+            const int at = ws.off[l] + (k8 * 8 + j) * C + c;
+            const float g = gv[j] * scale;
+            vv[j] = __builtin_fmaf(alpha, vv[j], oma * g * g);
+            tv[j] -= lr * g / sqrtf(vv[j] + eps);
+            v2[at] = vv[j]; th[at] = tv[j];
+        }
+        if (ws.split[l]) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) split3_pack(tv[2 * j], tv[2 * j + 1], hi[j], mid[j], lo[j]);
-                    const int plane = ws.plane(l);
-                    bf16_t* d = ws.split[l] + (size_t)((((c >> 5) * (K >> 4) + (k8 >> 1)) * 64 + (k8 & 1) * 32 + (c & 31)) * 8);
-                    *reinterpret_cast<uint4*>(d) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-                    *reinterpret_cast<uint4*>(d + plane) = make_uint4(mid[0], mid[1], mid[2], mid[3]);
-                    *reinterpret_cast<uint4*>(d + 2 * plane) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-                }
-                auto bf = [](float f) { __bf16 b = (__bf16)f; return (unsigned)__builtin_bit_cast(unsigned short, b); };
-                for (int d = 0; d < 2; ++d) {
-                    bf16_t* dst = ws.copy[l][d];
-                    if (!dst) continue;
-                    const int mode = ws.mode[l][d];
-                    if (mode == 0 || mode == 3) {          // k-contiguous: one 16-byte store
-                        const uint4 w = make_uint4(bf(tv[0]) | (bf(tv[1]) << 16), bf(tv[2]) | (bf(tv[3]) << 16),
-                                                   bf(tv[4]) | (bf(tv[5]) << 16), bf(tv[6]) | (bf(tv[7]) << 16));
-                        const size_t at = mode == 0 ? (size_t)c * K + k8 * 8 : ((size_t)k8 * max(C, 32) + c) * 8;
-                        *reinterpret_cast<uint4*>(dst + at) = w;
-                    } else if (mode == 1) {                // the matrix as it is: lanes write consecutive columns
+            for (int j = 0; j < 4; ++j) split3_pack(tv[2 * j], tv[2 * j + 1], hi[j], mid[j], lo[j]);
+            const int plane = ws.plane(l);
+            bf16_t* d = ws.split[l] + (size_t)((((c >> 5) * (K >> 4) + (k8 >> 1)) * 64 + (k8 & 1) * 32 + (c & 31)) * 8);
+            *reinterpret_cast<uint4*>(d) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+            *reinterpret_cast<uint4*>(d + plane) = make_uint4(mid[0], mid[1], mid[2], mid[3]);
+            *reinterpret_cast<uint4*>(d + 2 * plane) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+        }
+        auto bf = [](float f) { __bf16 b = (__bf16)f; return (unsigned)__builtin_bit_cast(unsigned short, b); };
+        for (int d = 0; d < 2; ++d) {
+            bf16_t* dst = ws.copy[l][d];
+            if (!dst) continue;
+            const int mode = ws.mode[l][d];
+            if (mode == 0 || mode == 3) {          // k-contiguous: one 16-byte store
+                const uint4 w = make_uint4(bf(tv[0]) | (bf(tv[1]) << 16), bf(tv[2]) | (bf(tv[3]) << 16),
+                                           bf(tv[4]) | (bf(tv[5]) << 16), bf(tv[6]) | (bf(tv[7]) << 16));
+                const size_t at = mode == 0 ? (size_t)c * K + k8 * 8 : ((size_t)k8 * max(C, 32) + c) * 8;
+                *reinterpret_cast<uint4*>(dst + at) = w;
+            } else if (mode == 1) {                // the matrix as it is: lanes write consecutive columns
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) dst[(size_t)(k8 * 8 + j) * C + c] = (bf16_t)bf(tv[j]);
-                    } else {                               // [ci][tap][co]: eight consecutive k are eight channels of one tap
-                        const int cin = ws.cin[l], T = K / cin, tap = (k8 * 8) / cin, ci0 = (k8 * 8) % cin;
+                for (int j = 0; j < 8; ++j) dst[(size_t)(k8 * 8 + j) * C + c] = (bf16_t)bf(tv[j]);
+            } else {                               // [ci][tap][co]: eight consecutive k are eight channels of one tap
+                const int cin = ws.cin[l], T = K / cin, tap = (k8 * 8) / cin, ci0 = (k8 * 8) % cin;
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) dst[((size_t)(ci0 + j) * T + tap) * C + c] = (bf16_t)bf(tv[j]);
-                    }
-                }
-                break;
+                for (int j = 0; j < 8; ++j) dst[((size_t)(ci0 + j) * T + tap) * C + c] = (bf16_t)bf(tv[j]);
             }
-            u -= units;
         }
         return;
     }
@@ -876,21 +910,30 @@ __global__ __launch_bounds__(256) void rmsprop_update_kernel(int n4, float4* the
             if (e0 >= 0 && e0 < ws.K[l] * ws.C[l]) return;         // updated above
         }
         g.x *= scale; g.y *= scale; g.z *= scale; g.w *= scale;
-        v.x = alpha * v.x + oma * g.x * g.x; v.y = alpha * v.y + oma * g.y * g.y;
-        v.z = alpha * v.z + oma * g.z * g.z; v.w = alpha * v.w + oma * g.w * g.w;
+        // (which product is rounded before the sum is written out, not left to the compiler)
+        v.x = __builtin_fmaf(oma * g.x, g.x, alpha * v.x); v.y = __builtin_fmaf(oma * g.y, g.y, alpha * v.y);
+        v.z = __builtin_fmaf(oma * g.z, g.z, alpha * v.z); v.w = __builtin_fmaf(oma * g.w, g.w, alpha * v.w);
         t.x -= lr * g.x / sqrtf(v.x + eps); t.y -= lr * g.y / sqrtf(v.y + eps);
         t.z -= lr * g.z / sqrtf(v.z + eps); t.w -= lr * g.w / sqrtf(v.w + eps);
         g2[i] = v; theta[i] = t;
     };
     const int stride = (gridDim.x - ws_blocks) * 256;
     int i = (blockIdx.x - ws_blocks) * 256 + threadIdx.x;
-    for (; i + stride < n4; i += 2 * stride) {                    // two elements' loads in flight
-        const float4 ga = grads[i], va = g2[i], ta = theta[i];
-        const float4 gb = grads[i + stride], vb = g2[i + stride], tb = theta[i + stride];
+    // two elements' loads in flight (past the end: the last element again, not used)
+    float4 ga, va, ta, gb, vb, tb;
+    auto load = [&]() __attribute__((always_inline)) {
+        const int a = min(i, n4 - 1), b = min(i + stride, n4 - 1);
+        ga = grads[a]; va = g2[a]; ta = theta[a];
+        gb = grads[b]; vb = g2[b]; tb = theta[b];
+    };
+    load();
+    find_norm();
+    while (i < n4) {
         update(i, ga, va, ta);
-        update(i + stride, gb, vb, tb);
+        if (i + stride < n4) update(i + stride, gb, vb, tb);
+        i += 2 * stride;
+        if (i < n4) load();
     }
-    if (i < n4) update(i, grads[i], g2[i], theta[i]);
     if ((int)blockIdx.x == ws_blocks && threadIdx.x < 64) {
         // lane l adds the partials l, l + 64, ... in ascending order, then the lanes are added: a fixed order
         float pl = 0.f, en = 0.f, vl = 0.f;
@@ -914,9 +957,12 @@ hipError_t rmsprop_update(hipStream_t s, int p_int, float* theta, float* g2, con
     const int n4 = p_int / 4;
     int blocks = (n4 + 255) / 256;
     if (blocks > 512) blocks = 512;       // grid-stride loop: fewer, longer-lived workgroups
-    int units = 0;
-    for (int l = 0; l < ws.n; ++l) units += (ws.K[l] / 8) * ws.C[l];
-    const int ws_blocks = (units + 255) / 256;
+    int ws_blocks = 0;
+    for (int l = 0; l < ws.n; ++l) {
+        const int cw = ws.C[l] < 64 ? ws.C[l] : 64;
+        if (256 % cw != 0 || ws.C[l] % cw != 0 || (ws.K[l] / 8) % (256 / cw) != 0) return hipErrorInvalidValue;       // whole workgroups
+        ws_blocks += (ws.K[l] / 8) * ws.C[l] / 256;
+    }
     launch_k(rmsprop_update_kernel, dim3(ws_blocks + blocks), dim3(256), s, n4, (float4*)theta, (float4*)g2,
                        (const float4*)grads, block_ss, n_ss, hp, loss_partials, n_loss_blocks, stats_a, stats_b,
                        ws, ws_blocks);

@@ -225,6 +225,15 @@ def test_train_ragged_and_degenerate(paac, oracle, net, n_e, t_max, p_done):
     check_train(oracle, net, ctx, params, rms, ro, I.HParams(clip_norm=0.01, lr=0.003), "clip")
 
 
+@pytest.mark.parametrize("n_actions", [2, 31, 32])
+def test_train_head_bias_gradients_with_many_chunks(paac, oracle, n_actions):
+    """More than eight partial sums of the few head biases, up to the largest action set."""
+    net = I.nips_net(n_actions)
+    ctx = make_ctx(paac, net, 24, 6)
+    ro = I.make_rollout(31, net, 24, 6, 0.05)
+    check_train(oracle, net, ctx, I.make_params(31, net, bias_range=0.05), I.make_rms(31, net, hi=0.01), ro, I.HParams(lr=0.002))
+
+
 def test_train_nature_above_one_sample_per_compute_unit(paac, oracle):
     """312 forward rows: more than one sample per compute unit, so the fp32 forward pass of layers 2-3
     runs in the per-layer kernels on exact bf16 parts (a workgroup walks over several samples)."""
