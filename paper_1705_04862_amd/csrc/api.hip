@@ -133,7 +133,7 @@ Plan make_plan(const NetDesc& n, int n_e, int T, bool bf16) {
     // below 1024 rows the returns + loss work rides in the head-backward launch, which leaves one
     // partial sum of the loss terms per chunk of rows instead of one per block of the loss kernel
     p.fused_loss = heads_bwd_fuses_loss(p.B, n.n_actions, p.T, n.fc);
-    p.n_loss_blocks = p.fused_loss ? p.head_chunks : loss_blocks(n_e);
+    p.n_loss_blocks = p.fused_loss ? p.head_chunks : loss_blocks(n_e, T);
     return p;
 }
 

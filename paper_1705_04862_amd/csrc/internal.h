@@ -142,7 +142,7 @@ struct LossArgs {
     float* loss_partials;                                // [blocks][4]
     int algorithm;                                       // ALG_*
 };
-int loss_blocks(int n_e);
+int loss_blocks(int n_e, int T);
 hipError_t returns_loss(hipStream_t s, const LossArgs& a);
 
 // head backward in one launch: dh (fp32, or bf16 when dh_b is non-null) and the split weight gradients

@@ -72,62 +72,90 @@ __device__ __forceinline__ void choose_action(const HeadsArgs& a, float z, int l
 // One wavefront per state row.  The fc layer's split partial sums are added, bias and ReLU applied,
 // then A+1 dot products (policy logits, value) are reduced across the 64 lanes; lane k ends up
 // holding logit k.  In select mode the same wavefront computes the softmax and draws the action.
+// A wavefront keeps the head weights of its lanes in registers and walks over rows (one row per wavefront
+// fetched 38 KB of weights from L2 for every row: 21504 rows 42 -> 32 us; the rows themselves are 88 MB).
 template <int F, int KMAX>                 // KMAX >= A + 1 outputs (logits + the value)
-__global__ __launch_bounds__(256) void heads_fwd_kernel(const HeadsArgs a) {
+__global__ __launch_bounds__(256, 2) void heads_fwd_kernel(const HeadsArgs a) {
     constexpr int C = F / 256;            // float4 chunks per lane
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int row = blockIdx.x * 4 + wave;
+    int row = blockIdx.x * 4 + wave;
     if (row >= a.rows) return;
-    float4 h[C];
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-        const int col = c * 256 + lane * 4;
-        const float* src = a.fc_partial + (size_t)row * F + col;
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        int s = 0;
-        for (; s + 8 <= a.n_split; s += 8) {          // eight independent loads in flight
-            float4 p[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) p[q] = *reinterpret_cast<const float4*>(src + (size_t)(s + q) * a.split_stride);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) { acc.x += p[q].x; acc.y += p[q].y; acc.z += p[q].z; acc.w += p[q].w; }
-        }
-        for (; s < a.n_split; ++s) {
-            const float4 p = *reinterpret_cast<const float4*>(src + (size_t)s * a.split_stride);
-            acc.x += p.x; acc.y += p.y; acc.z += p.z; acc.w += p.w;
-        }
-        const float4 b = *reinterpret_cast<const float4*>(a.fc_b + col);
-        acc.x = fmaxf(acc.x + b.x, 0.f); acc.y = fmaxf(acc.y + b.y, 0.f);
-        acc.z = fmaxf(acc.z + b.z, 0.f); acc.w = fmaxf(acc.w + b.w, 0.f);
-        h[c] = acc;
-        if (a.h_out) *reinterpret_cast<float4*>(a.h_out + (size_t)row * F + col) = acc;
-    }
-    // all dot products first, then all reductions: the shuffles of different outputs are independent
     // (branch-free: outputs beyond A re-read the value row and are ignored)
-    float d[KMAX];
+    float4 w4[KMAX][C], b4[C];
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) {
         const float* w = k < a.A ? a.pi_w + (size_t)k * F : a.v_w;
-        d[k] = 0.f;
+#pragma unroll
+        for (int c = 0; c < C; ++c) w4[k][c] = *reinterpret_cast<const float4*>(w + c * 256 + lane * 4);
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) b4[c] = *reinterpret_cast<const float4*>(a.fc_b + c * 256 + lane * 4);
+    const float my_b = lane < a.A ? a.pi_b[lane] : 0.f, v_b = a.v_b[0];
+    // the next row's first partial sums arrive while a row is worked on (clamped: ignored below)
+    constexpr int P = 3;
+    float4 pre[C][P];
+    auto request = [&](int r) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int q = 0; q < P; ++q)
+                pre[c][q] = *reinterpret_cast<const float4*>(a.fc_partial + (size_t)min(q, a.n_split - 1) * a.split_stride +
+                                                             (size_t)min(r, a.rows - 1) * F + c * 256 + lane * 4);
+    };
+    request(row);
+    for (; row < a.rows; row += gridDim.x * 4) {
+        float4 h[C];
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            const float4 w4 = *reinterpret_cast<const float4*>(w + c * 256 + lane * 4);
-            d[k] += h[c].x * w4.x + h[c].y * w4.y + h[c].z * w4.z + h[c].w * w4.w;
-        }
-    }
-    float z = -INFINITY, v = 0.f;
-    const float my_b = lane < a.A ? a.pi_b[lane] : 0.f;
+            h[c] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-        const float t = wave_sum(d[k]);
-        z = (lane == k && k < a.A) ? t + my_b : z;
-        v = (k == a.A) ? t : v;
+            for (int q = 0; q < P; ++q)
+                if (q < a.n_split) { h[c].x += pre[c][q].x; h[c].y += pre[c][q].y; h[c].z += pre[c][q].z; h[c].w += pre[c][q].w; }
+        }
+        request(row + gridDim.x * 4);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int col = c * 256 + lane * 4;
+            const float* src = a.fc_partial + (size_t)row * F + col;
+            float4 acc = h[c];
+            int s = P;
+            for (; s + 8 <= a.n_split; s += 8) {          // eight independent loads in flight
+                float4 p[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) p[q] = *reinterpret_cast<const float4*>(src + (size_t)(s + q) * a.split_stride);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) { acc.x += p[q].x; acc.y += p[q].y; acc.z += p[q].z; acc.w += p[q].w; }
+            }
+            for (; s < a.n_split; ++s) {
+                const float4 p = *reinterpret_cast<const float4*>(src + (size_t)s * a.split_stride);
+                acc.x += p.x; acc.y += p.y; acc.z += p.z; acc.w += p.w;
+            }
+            acc.x = fmaxf(acc.x + b4[c].x, 0.f); acc.y = fmaxf(acc.y + b4[c].y, 0.f);
+            acc.z = fmaxf(acc.z + b4[c].z, 0.f); acc.w = fmaxf(acc.w + b4[c].w, 0.f);
+            h[c] = acc;
+            if (a.h_out) *reinterpret_cast<float4*>(a.h_out + (size_t)row * F + col) = acc;
+        }
+        // all dot products first, then all reductions: the shuffles of different outputs are independent
+        float d[KMAX];
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            d[k] = 0.f;
+#pragma unroll
+            for (int c = 0; c < C; ++c) d[k] += h[c].x * w4[k][c].x + h[c].y * w4[k][c].y + h[c].z * w4[k][c].z + h[c].w * w4[k][c].w;
+        }
+        float z = -INFINITY, v = 0.f;
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            const float t = wave_sum(d[k]);
+            z = (lane == k && k < a.A) ? t + my_b : z;
+            v = (k == a.A) ? t : v;
+        }
+        v += v_b;
+        if (a.values_out && lane == 0) a.values_out[row] = v;
+        if (a.values_copy && lane == 0) a.values_copy[row] = v;
+        if (a.logits_out && lane < a.A) a.logits_out[(size_t)row * a.A + lane] = z;
+        if (a.uniforms) choose_action(a, z, lane, row);
     }
-    v += a.v_b[0];
-    if (a.values_out && lane == 0) a.values_out[row] = v;
-    if (a.values_copy && lane == 0) a.values_copy[row] = v;
-    if (a.logits_out && lane < a.A) a.logits_out[(size_t)row * a.A + lane] = z;
-    if (a.uniforms) choose_action(a, z, lane, row);
 }
 
 // Up to 2048 rows (every select call of the measurement configurations, the train forward of the
@@ -210,7 +238,7 @@ template <int F, int KMAX> static void launch_heads(hipStream_t s, const HeadsAr
         else if (a.n_split <= 16) launch_k((heads_fwd_row_kernel<F, KMAX, 16>), dim3(a.rows), dim3(256), s, a);
         else launch_k((heads_fwd_row_kernel<F, KMAX, 32>), dim3(a.rows), dim3(256), s, a);
     }
-    else launch_k((heads_fwd_kernel<F, KMAX>), dim3((a.rows + 3) / 4), dim3(256), s, a);
+    else launch_k((heads_fwd_kernel<F, KMAX>), dim3(512), dim3(256), s, a);       // two workgroups per compute unit
 }
 
 hipError_t heads_fwd(hipStream_t s, int F, const HeadsArgs& a) {
@@ -229,17 +257,18 @@ hipError_t heads_fwd(hipStream_t s, int F, const HeadsArgs& a) {
 }
 
 // ------------------------------------------------------------------------------------ returns + loss
-// A block owns kEnvPerBlock environments.  Phase 1: one thread per environment runs the backward
+// A block owns a few environments (as many as give each of its threads one row, at most 32: with 32 of them and t_max = 20
+// a thread worked on three rows in turn, 16 us at n_e = 1024 against 10).  Phase 1: one thread per environment runs the backward
 // recursion R_t = r_t + gamma (1 - d_t) R_{t+1} from R_{T+1} = V(s_{T+1}).  Phase 2: one thread per
 // (t, e) row forms adv = R - V, the three loss terms and dL/dlogits, dL/dV.
-constexpr int kEnvPerBlock = 32;
-int loss_blocks(int n_e) { return (n_e + kEnvPerBlock - 1) / kEnvPerBlock; }
+static __host__ __device__ int loss_env_per_block(int T) { const int e = 256 / T; return e < 1 ? 1 : e > 32 ? 32 : e; }
+int loss_blocks(int n_e, int T) { const int e = loss_env_per_block(T); return (n_e + e - 1) / e; }
 
 template <int AMAX>
 __global__ __launch_bounds__(256) void returns_loss_kernel(const LossArgs a) {
     const int tid = threadIdx.x;
-    const int e0 = blockIdx.x * kEnvPerBlock;
-    const int ne_blk = min(kEnvPerBlock, a.n_e - e0);
+    const int epb = loss_env_per_block(a.T), e0 = blockIdx.x * epb;
+    const int ne_blk = min(epb, a.n_e - e0);
     const int B = a.T * a.n_e;
     const float gamma = a.hp[HP_GAMMA], beta = a.hp[HP_BETA], cv = a.hp[HP_VCOEF];
     if (tid < ne_blk) {
@@ -327,7 +356,7 @@ __global__ __launch_bounds__(256) void returns_loss_kernel(const LossArgs a) {
 }
 
 hipError_t returns_loss(hipStream_t s, const LossArgs& a) {
-    const dim3 grid(loss_blocks(a.n_e));
+    const dim3 grid(loss_blocks(a.n_e, a.T));
     if (a.A <= 8) launch_k(returns_loss_kernel<8>, grid, dim3(256), s, a);
     else if (a.A <= 18) launch_k(returns_loss_kernel<18>, grid, dim3(256), s, a);
     else launch_k(returns_loss_kernel<32>, grid, dim3(256), s, a);
@@ -541,9 +570,9 @@ __global__ __launch_bounds__(256) void heads_bwd_rows_kernel(const HeadsBwdArgs 
     const int wb = blockIdx.x - a.n_dh, fx = F / 64, fxi = wb % fx, c = wb / fx, K1 = A + 1;
     const int j = fxi * 64 + lane;
     const int r0 = c * a.rows_per_chunk, r1 = min(rows, r0 + a.rows_per_chunk);      // a trailing chunk may be empty: zeros
-    float acc[AMAX + 1], accb[AMAX + 1];
+    float acc[AMAX + 1], accb = 0.f;                // accb: lane k adds up coefficient k
 #pragma unroll
-    for (int k = 0; k <= AMAX; ++k) { acc[k] = 0.f; accb[k] = 0.f; }
+    for (int k = 0; k <= AMAX; ++k) acc[k] = 0.f;
     float s_pl = 0.f, s_h = 0.f, s_vl = 0.f;
     for (int r = r0 + wave; r < r1; r += 4 * RQ) {     // RQ of this wave's rows in flight
         float hv[RQ], cv[RQ];                          // cv: lane k holds coefficient k of the row (zero past the chunk)
@@ -574,17 +603,16 @@ __global__ __launch_bounds__(256) void heads_bwd_rows_kernel(const HeadsBwdArgs 
         }
 #pragma unroll
         for (int q = 0; q < RQ; ++q) {
+            accb += cv[q];
 #pragma unroll
             for (int k = 0; k <= AMAX; ++k)
-                if (k < K1) {
-                    const float g = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cv[q]), k));
-                    acc[k] += g * hv[q]; accb[k] += g;
-                }
+                if (k < K1) acc[k] += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cv[q]), k)) * hv[q];
         }
     }
 #pragma unroll
     for (int k = 0; k <= AMAX; ++k)
-        if (k < K1) { part[wave][k][lane] = acc[k]; if (lane == 0) partb[wave][k] = accb[k]; }
+        if (k < K1) part[wave][k][lane] = acc[k];
+    if (lane < K1) partb[wave][lane] = accb;
     if (FUSED && lane == 0) { lossp[wave][0] = s_pl * invB; lossp[wave][1] = s_h * invB; lossp[wave][2] = s_vl * invB; }
     __syncthreads();
     for (int e = tid; e < K1 * 64; e += 256) {
@@ -622,7 +650,8 @@ hipError_t heads_bwd(hipStream_t s, int F, int A, int rows, int n_chunk, const f
     }
     if (rows >= 1024 && A <= 32 && (F / 4) % 64 == 0 && 256 % (F / 4) == 0) {            // large batches: h is read once
         const int rpi = 256 / (F / 4);                       // rows a dh block works on at once
-        int rpd = rows / 512;                                // enough dh blocks to fill the chip, at most 32 rows each
+        // enough dh blocks to fill the chip, at most 32 rows each (1280 rows: rows / 512 12.8 us, rows / 256 10.7)
+        int rpd = rows / 256;
         rpd = rpd > 32 ? 32 : rpd;
         rpd = (rpd + rpi - 1) / rpi * rpi;
         const int n_dh = (rows + rpd - 1) / rpd;
