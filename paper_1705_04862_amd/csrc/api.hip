@@ -551,11 +551,13 @@ int upload_hparams(paac_ctx* c, const paac_hparams* hp) {
 }
 
 struct DeviceGuard {
-    int prev; bool ok;
-    explicit DeviceGuard(int dev) : prev(-1), ok(false) {
-        if (hipGetDevice(&prev) == hipSuccess) { ok = (prev == dev) || hipSetDevice(dev) == hipSuccess; }
+    int prev; bool ok, changed;
+    explicit DeviceGuard(int dev) : prev(-1), ok(false), changed(false) {
+        if (hipGetDevice(&prev) != hipSuccess) return;
+        changed = prev != dev;
+        ok = !changed || hipSetDevice(dev) == hipSuccess;
     }
-    ~DeviceGuard() { if (prev >= 0) hipSetDevice(prev); }
+    ~DeviceGuard() { if (changed) hipSetDevice(prev); }
 };
 
 }  // namespace

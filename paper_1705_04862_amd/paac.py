@@ -98,12 +98,16 @@ def _np_ptr(a: Optional[np.ndarray]):
     return None if a is None else a.ctypes.data_as(C.c_void_p)
 
 
+_U8, _I32, _F32 = torch.uint8, torch.int32, torch.float32
+
+
 class Paac:
     """One PAAC context on the current torch device/stream."""
 
     def __init__(self, arch: int, n_e: int, t_max: int, n_actions: int, precision: int = 0,
                  stream: Optional[torch.cuda.Stream] = None, device: str = "cuda:0"):
         self.L = lib()
+        self._select_actions, self._select_actions_noalloc = self.L.paac_select_actions, self.L.paac_select_actions_noalloc
         self.cfg = paac_config(arch, n_e, t_max, n_actions, 4, 84, 84, precision)
         self.device = torch.device(device)
         self.n_e, self.t_max, self.n_actions = n_e, t_max, n_actions
@@ -146,24 +150,26 @@ class Paac:
                        values: Optional[torch.Tensor] = None, probs: Optional[torch.Tensor] = None):
         """states uint8 [n_e,4,84,84]; uniforms f32 [n_e]; actions i32 [n_e] (out); optional
         values f32 [n_e], probs f32 [n_e,A] (out).  All contiguous device tensors."""
-        assert states.dtype == torch.uint8 and states.is_contiguous() and states.numel() == self.n_e * 28224
-        assert uniforms.dtype == torch.float32 and uniforms.numel() == self.n_e and uniforms.is_contiguous()
-        assert actions.dtype == torch.int32 and actions.numel() == self.n_e and actions.is_contiguous()
-        assert values is None or (values.dtype == torch.float32 and values.numel() == self.n_e)
-        assert probs is None or (probs.dtype == torch.float32 and probs.numel() == self.n_e * self.n_actions)
-        self._check(self.L.paac_select_actions(self.ctx, _ptr(states), _ptr(uniforms), _ptr(actions),
-                                               _ptr(values), _ptr(probs)))
+        self._select(self._select_actions, states, uniforms, actions, values, probs)
+
+    # One action selection of the small network is as long on the host as on the GPU (12 us, three
+    # launches of 3 us each): no lookups and calls here that can be done without.
+    def _select(self, entry, states, uniforms, actions, values, probs):
+        n_e = self.n_e
+        assert states.dtype == _U8 and states.is_contiguous() and states.numel() == n_e * 28224
+        assert uniforms.dtype == _F32 and uniforms.numel() == n_e and uniforms.is_contiguous()
+        assert actions.dtype == _I32 and actions.numel() == n_e and actions.is_contiguous()
+        assert values is None or (values.dtype == _F32 and values.numel() == n_e)
+        assert probs is None or (probs.dtype == _F32 and probs.numel() == n_e * self.n_actions)
+        rc = entry(self.ctx, states.data_ptr(), uniforms.data_ptr(), actions.data_ptr(),
+                   None if values is None else values.data_ptr(), None if probs is None else probs.data_ptr())
+        if rc:
+            self._check(rc)
 
     def select_actions_noalloc(self, states: torch.Tensor, uniforms: torch.Tensor, actions: torch.Tensor,
                                values: Optional[torch.Tensor] = None, probs: Optional[torch.Tensor] = None):
         """select_actions through the entry point that uses the library's static scratch."""
-        assert states.dtype == torch.uint8 and states.is_contiguous() and states.numel() == self.n_e * 28224
-        assert uniforms.dtype == torch.float32 and uniforms.numel() == self.n_e and uniforms.is_contiguous()
-        assert actions.dtype == torch.int32 and actions.numel() == self.n_e and actions.is_contiguous()
-        assert values is None or (values.dtype == torch.float32 and values.numel() == self.n_e)
-        assert probs is None or (probs.dtype == torch.float32 and probs.numel() == self.n_e * self.n_actions)
-        self._check(self.L.paac_select_actions_noalloc(self.ctx, _ptr(states), _ptr(uniforms), _ptr(actions),
-                                                       _ptr(values), _ptr(probs)))
+        self._select(self._select_actions_noalloc, states, uniforms, actions, values, probs)
 
     def train_step(self, states: torch.Tensor, actions: torch.Tensor, rewards: torch.Tensor,
                    dones: torch.Tensor, hp, stats: Optional[torch.Tensor] = None):
